@@ -9,20 +9,34 @@
 //   q_v = rint(e_v * 2^40)                  (integer mass, 0 .. 2^40)
 //   S   = sum_v q_v
 //   nucleus: the shortest prefix of the tokens ordered by (q desc, index asc)
-//            whose mass reaches ceil(p24 * S / 2^24), p24 = rint(top_p * 2^24)
+//            whose mass reaches T_p = ceil(p24 * S / 2^24), p24 = rint(top_p * 2^24)
 //   Z   = nucleus mass, target = floor(u24 * Z / 2^24), u24 = floor(u * 2^24)
 //   token = the first nucleus token, in index order, whose running nucleus
 //           mass exceeds target.
 //
-// One work group of 1024 threads per row.  The nucleus threshold key is
-// found by a radix select over the 41-bit keys (digits of 11, 11, 11 and 8
-// bits) with 64-bit integer mass histograms in LDS (integer atomics: the
-// result does not depend on their order); the final index-order walk uses
-// wave-level scans over each wave's contiguous range.  Only the first round
-// needs every token's mass.  Later passes need only the tokens whose mass can
-// fall in the current key range.  A conservative test on x = (z - max z)/T
-// (the mass is monotone in x) selects them, and only they recompute the
-// exponential, so every decision stays exact without a stored row of keys.
+// The threshold key kappa (the largest key with mass{q >= kappa} >= T_p) is
+// found in the order of x = (z - max z)/T, in which the masses are monotone:
+//   1. the row maximum;
+//   2. every token's mass into a histogram over x (16 bins an octave, 64-bit
+//      integer LDS atomics, so their order does not matter); its total is S
+//      and the bin that crosses T_p holds the threshold;
+//   3. a second pass sums, per index block, the masses above that bin and
+//      lists the bin's own tokens (a few hundred of 128K);
+//   4. kappa, the ties at kappa that join the nucleus (lowest indices first)
+//      and each block's nucleus mass follow from the list alone;
+//   5. only the index block that holds the target is walked token by token.
+// So a row is read three times and each token's exponential is evaluated once,
+// plus once more for nucleus members; a radix select over the keys themselves
+// re-evaluates it in every round whose digit range holds most of the row.  At
+// 128256 logits N(0, 9), T 0.8, top_p 0.95, against that radix select: 256 rows
+// (one work group each) 104 us instead of 323, 16 rows (the split form) 37 us
+// instead of 136.  What is left at 256 rows: the three passes (18 us at the HBM
+// rate, ~45 of fp64 arithmetic, ~30 for the second pass) and ~12 of decisions.
+// With top_p = 1 the nucleus is every token of nonzero mass: steps 2 to 4
+// reduce to the per-block masses.  Two rare shapes of row take a radix select
+// over the 41-bit keys instead (radix_threshold): a threshold bin with more
+// tokens than the list holds, and thresholds so deep (masses below 64) that one
+// key spans several bins.
 #include "hip_common.h"
 #include "kernels.h"
 
@@ -34,21 +48,29 @@ namespace pdec {
 namespace {
 
 constexpr int kThreads = 1024, kWaves = kThreads / 64;
-constexpr int kUnroll = 8;  // loads in flight per lane: index slabs of 64
-constexpr int kUnroll4 = 4;  // 16-byte loads in flight per lane (vectorised passes)
-constexpr int kRounds = 4, kMaxBins = 2048;
-// Radix digits of the 41-bit keys, most significant first: bits 40..30,
-// 29..19, 18..8, 7..0.
-__device__ constexpr int kShift[kRounds] = {30, 19, 8, 0};
-__device__ constexpr int kWidth[kRounds] = {11, 11, 11, 8};
+constexpr int kBins = 1024;        // histogram bins, one per thread of a row's group
+constexpr double kOctave = 16.0;   // step 2: bins per factor of two of the mass (670 of them)
+constexpr int kMaxBlocks = 128;    // index blocks of a row
+constexpr int kSlab = 512;         // tokens a wave holds at a time, 8 per lane
+constexpr int kListCap = 8192;     // threshold-bin tokens held in LDS
+constexpr double kMinX = -28.5;    // below it the mass rounds to 0
+constexpr double kLn2 = 0.69314718055994530942;
+constexpr double kMinKey = 64.0;   // step 3 needs one key to stay within about one bin
 typedef unsigned __int128 u128;
 
-// Integer mass of one logit.  Below x = -28.5 the exponential is under
-// 2^-41 and the mass rounds to exactly 0, so the exponential is skipped.
-__device__ __forceinline__ uint64_t mass_of(float z, double m, double inv_t) {
-  const double x = ((double)z - m) * inv_t;
-  if (x < -28.5) return 0;
-  return (uint64_t)rint(exp(x) * 0x1p40);
+// Length of a row's index blocks (a multiple of 256): at most kMaxBlocks of
+// them, 1024 tokens each for the 128256-token vocabulary.
+__host__ __device__ __forceinline__ int block_len(int V) {
+  const int64_t b = ((int64_t)V + kMaxBlocks - 1) / kMaxBlocks;
+  return (int)((b + 255) / 256 * 256);
+}
+
+// Integer mass at x <= 0 (NaN: 0).  Below x = -28.5 the exponential is under
+// 2^-41 and the mass rounds to exactly 0.  Adding 2^52 rounds e * 2^40 to an
+// integer (to nearest even, as rint) and leaves it in the mantissa bits.
+__device__ __forceinline__ uint64_t mass_at(double x) {
+  if (!(x >= kMinX)) return 0;
+  return __double_as_longlong(__builtin_fma(exp(x), 0x1p40, 0x1p52)) - 0x4330000000000000ull;
 }
 
 __device__ __forceinline__ uint64_t wave_scan_incl(uint64_t v, int lane) {
@@ -66,6 +88,12 @@ __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
   return v;
 }
 
+__device__ __forceinline__ uint64_t lane_u64(uint64_t v, int lane) {  // lane uniform
+  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane);
+  return ((uint64_t)hi << 32) | lo;
+}
+
 // Lowest x whose mass can reach key k (k >= 1): rint(e * 2^40) >= k needs
 // e * 2^40 >= k - 1/2; a margin far above the exponential's error keeps the
 // test conservative.
@@ -73,548 +101,845 @@ __device__ __forceinline__ double x_floor(uint64_t k) {
   return k == 0 ? -INFINITY : log(((double)k - 0.5) * 0x1p-40) - 1e-9;
 }
 
-__global__ __launch_bounds__(kThreads) void sample_top_p_kernel(
-    int V, const float* __restrict__ logits, double inv_t, uint32_t p24,
-    const float* __restrict__ uniforms, int32_t* __restrict__ tokens) {
-  __shared__ uint64_t hist[kMaxBins];
-  __shared__ uint64_t wave_a[kWaves], wave_b[kWaves];
-  __shared__ float red_f[kWaves];
-  __shared__ uint64_t sel[3];  // digit, mass above it, T_p
+// One row as a wave reads it: 8 tokens per lane of a slab of kSlab tokens.
+// VEC: 16-byte loads (the row starts 16-byte aligned and V % 4 == 0).
+template <bool VEC>
+struct Row {
+  const float* z;
+  int V, blen, nb;
+  double m, inv_t;
+  // Not to be fused into what a caller does with it: two callers have to see
+  // the same x for the same logit.
+  __device__ __forceinline__ double x(float v) const {
+#pragma clang fp contract(off)
+    return ((double)v - m) * inv_t;
+  }
+  // The lane's tokens of the slab at token `at`, loads only: indices past the
+  // row's end read its last tokens, and mask() turns them into -inf once the
+  // loads are waited for.
+  __device__ __forceinline__ void load(int at, int lane, float (&v)[8]) const {
+    const int last = V - 1 - at;
+#pragma unroll
+    for (int u = 0; u < 8; u += VEC ? 4 : 1) {
+      if constexpr (VEC) {
+        const float4 f = *(const float4*)(z + at + min(u * 64 + 4 * lane, last - 3));
+        v[u] = f.x;
+        v[u + 1] = f.y;
+        v[u + 2] = f.z;
+        v[u + 3] = f.w;
+      } else {
+        v[u] = z[at + min(u * 64 + lane, last)];
+      }
+    }
+  }
+  // n: tokens of the slab that belong to the block.
+  __device__ __forceinline__ void mask(int n, int lane, const float (&w)[8], float (&v)[8]) const {
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      v[u] = (VEC ? (u & 4) * 64 + 4 * lane : u * 64 + lane) < n ? w[u] : -INFINITY;
+  }
+  // Index within the slab of a lane's element k of part `part`.
+  __device__ __forceinline__ int offset(int part, int k, int lane) const {
+    return part * 256 + (VEC ? 4 * lane + k : k * 64 + lane);
+  }
+  // f(block, first token, part, four of the lane's values, whether the block
+  // ends there) for both parts of every slab of blocks b, b + step, .. below
+  // b1, the next slab's loads in flight meanwhile.  The parts run through one
+  // copy of f's code: a launch runs it a few times per wave, and fetching 16
+  // unrolled copies of it cost more than running them (split_members: 20 us
+  // against 6).
+  template <typename F>
+  __device__ __forceinline__ void slabs(int b, int b1, int step, int lane, F&& f) const {
+    if (b >= b1) return;
+    int o = 0, n = min(blen, V - b * blen);
+    float v[8], w[8];
+    load(b * blen, lane, w);
+    mask(n, lane, w, v);
+    wait_vmem<0>();  // nothing but the next slab is in flight inside the loop
+    for (;;) {
+      const bool end = o + kSlab >= n;
+      const int b2 = end ? b + step : b, o2 = end ? 0 : o + kSlab;
+      const bool more = b2 < b1;
+      load(more ? b2 * blen + o2 : b * blen + o, lane, w);  // the last slab again at the end
+#pragma unroll 1
+      for (int part = 0; part < 2; ++part) {
+        float h[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) h[k] = part ? v[4 + k] : v[k];
+        f(b, b * blen + o, part, h, end && part);
+      }
+      if (!more) break;
+      b = b2;
+      o = o2;
+      n = min(blen, V - b * blen);
+      mask(n - o, lane, w, v);
+    }
+  }
+};
+
+template <bool VEC>
+__device__ __forceinline__ Row<VEC> make_row(int V, const float* logits, int b, double inv_t) {
+  Row<VEC> r;
+  r.z = logits + (int64_t)b * V;
+  r.V = V;
+  r.blen = block_len(V);
+  r.nb = (V - 1) / r.blen + 1;
+  r.m = 0.0;
+  r.inv_t = inv_t;
+  return r;
+}
+
+// The masses of a pass over a whole row.  mass_at takes about 60 operations in
+// one dependent chain (the pass took 51 us for 256 rows, one per CU, with or
+// without its LDS atomics).  Here, with the row's scale folded into one
+// constant and 2^(j/16) * 2^40 in a 16-entry LDS table (entries in distinct
+// banks): t = (z - max z) * 16 / (T ln 2) = n + r, |r| <= 1/2, and
+//   e * 2^40 = 2^(n >> 4) * table[n & 15] * exp(r ln2 / 16),
+// the last factor a Taylor polynomial of degree 6 (next term (ln2/32)^7 / 7! =
+// 4.5e-16).  With the roundings the product is within (1.5e-15 + 4e-16 |x|) of
+// exp(x) * 2^40, relatively, |x| <= 29, so below 1.4e-14; where that could
+// change the rounding to an integer (a distance under 4e-14 of the value to a
+// half: every 10^6th token at e = 2^-15), mass_at decides.  The keys are
+// therefore mass_at's, bit for bit.  -n also numbers the histogram's bins.
+struct FastMass {
+  double m, dmin, c1;
+  const double* table;  // LDS
+};
+__device__ __forceinline__ void fill_table(double* table) {  // then a barrier
+  if (threadIdx.x < 16) table[threadIdx.x] = exp2((double)threadIdx.x / 16.0 + 40.0);
+}
+__device__ __forceinline__ FastMass make_fast(double m, double inv_t, const double* table) {
+  return {m, -29.0 / inv_t, inv_t * (kOctave / kLn2), table};
+}
+// The keys of N logits (0 below x = -29 and for NaN) and their bins; bit k of
+// the result is set where mass_at has to decide.  The N chains of dependent fp64
+// operations run side by side.
+template <int N>
+__device__ __forceinline__ uint32_t fast_mass(const FastMass& fm, const float (&z)[N],
+                                              uint64_t (&q)[N], int (&bin)[N]) {
+  constexpr double kRound = 6755399441055744.0;  // 1.5 * 2^52: n in the low mantissa bits
+  constexpr double a = kLn2 / kOctave;
+  constexpr double coef[6] = {a * a * a * a * a / 120.0, a * a * a * a / 24.0, a * a * a / 6.0,
+                              a * a / 2.0, a, 1.0};
+  double r[N], p[N], tb[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const double d = fmax((double)z[k] - fm.m, fm.dmin);
+    const double un = __builtin_fma(d, fm.c1, kRound);
+    const int n = (int)(uint32_t)__double_as_longlong(un);
+    bin[k] = -n;
+    const int64_t t = __double_as_longlong(fm.table[n & 15]);
+    tb[k] = __longlong_as_double(t + ((int64_t)(n >> 4) << 52));
+    r[k] = __builtin_fma(d, fm.c1, -(un - kRound));
+    p[k] = a * a * a * a * a * a / 720.0;
+  }
+#pragma unroll
+  for (int c = 0; c < 6; ++c)
+#pragma unroll
+    for (int k = 0; k < N; ++k) p[k] = __builtin_fma(p[k], r[k], coef[c]);
+  uint32_t close = 0;
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const double v = tb[k] * p[k];
+    const double w = v + 0x1p52;
+    const double off = fabs(v - (w - 0x1p52));  // exact; 1/2 at a tie
+    close |= __builtin_fma(v, 4e-14, off) >= 0.5 ? 1u << k : 0u;
+    q[k] = (uint64_t)__double_as_longlong(w) & 0xFFFFFFFFFFFFFull;
+  }
+  return close;
+}
+
+// Element k of a lane's four values, k different per lane.
+template <typename T>
+__device__ __forceinline__ T pick4(const T (&v)[4], int k) {
+  const T a = k & 1 ? v[1] : v[0], b = k & 1 ? v[3] : v[2];
+  return k & 2 ? b : a;
+}
+
+// Step 2 for a part of a slab: masses into hist by bin.  Runs of equal bins in a lane
+// are added up first, so that a row of equal logits does not send four atomics
+// per lane to one address.
+template <bool VEC>
+__device__ __forceinline__ void slab_hist(const Row<VEC>& row, const FastMass& fm, const float (&v)[4],
+                                          uint64_t* hist) {
+  uint64_t q[4];
+  int bin[4];
+  uint32_t redo = fast_mass<4>(fm, v, q, bin);
+  if (__any(redo != 0)) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) q[k] = redo >> k & 1 ? 0 : q[k];
+    while (redo) {
+      const int k = __ffs(redo) - 1;
+      redo &= redo - 1;
+      const uint64_t e = mass_at(row.x(pick4(v, k)));
+      if (e) atomicAdd((unsigned long long*)&hist[pick4(bin, k)], e);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (k < 3 && bin[k] == bin[k + 1]) q[k + 1] += q[k];
+    else if (q[k]) atomicAdd((unsigned long long*)&hist[bin[k]], q[k]);
+  }
+}
+
+// Sum of the masses of the lane's tokens in mask, of which a lane usually has
+// none or one: each lane evaluates its own next one.
+template <bool VEC>
+__device__ __forceinline__ uint64_t slab_mass(const Row<VEC>& row, const FastMass& fm,
+                                              const float (&v)[4], uint32_t mask) {
+  uint64_t sum = 0;
+  while (mask) {
+    const float z[1] = {pick4(v, __ffs(mask) - 1)};
+    mask &= mask - 1;
+    uint64_t q[1];
+    int bin[1];
+    if (__builtin_expect(fast_mass<1>(fm, z, q, bin), 0)) q[0] = mass_at(row.x(z[0]));
+    sum += q[0];
+  }
+  return sum;
+}
+
+// Sum of all four masses.
+template <bool VEC>
+__device__ __forceinline__ uint64_t slab_mass_all(const Row<VEC>& row, const FastMass& fm,
+                                                  const float (&v)[4]) {
+  uint64_t q[4];
+  int bin[4];
+  uint32_t redo = fast_mass<4>(fm, v, q, bin);
+  uint64_t sum = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) sum += redo >> k & 1 ? 0 : q[k];
+  while (redo) {
+    sum += mass_at(row.x(pick4(v, __ffs(redo) - 1)));
+    redo &= redo - 1;
+  }
+  return sum;
+}
+
+// The bounds of step 3.  Logits at or above z1 are above every key of the
+// threshold bin: z1 lies past the bin's upper edge by what one key spans there
+// (and a slack for the roundings), so no token at or past it shares a key with
+// the bin.  Logits in [z0, z1) are listed; z0 lies below the bin's lower edge by
+// as much, so the list holds the whole bin and every token that shares a key
+// with it.
+struct Bounds {
+  float z0, z1;
+};
+template <bool VEC>
+__device__ __forceinline__ Bounds bin_bounds(const Row<VEC>& row, int bin) {
+  const double hi = (0.5 - bin) * (kLn2 / kOctave), lo = hi - kLn2 / kOctave;
+  const double z1 = row.m + (hi + 2.0 / (exp(hi) * 0x1p40) + 1e-9) / row.inv_t;
+  const double z0 = row.m + (lo - 2.0 / (exp(lo) * 0x1p40) - 1e-9) / row.inv_t;
+  return {(float)(z0 - fabs(z0) * 0x1p-22), (float)(z1 + fabs(z1) * 0x1p-22)};
+}
+// Whether one key spans more than about a bin there (masses below kMinKey).
+__device__ __forceinline__ bool bin_deep(int bin) {
+  return exp(-(double)bin * (kLn2 / kOctave)) * 0x1p40 < kMinKey;
+}
+
+// Step 3 for a part of a slab at token `at`: the lane's mass of tokens at or above z1
+// is returned, tokens of [z0, z1) go to the list (count in *n_list, which may
+// pass cap; only the first cap are stored).
+template <bool VEC>
+__device__ __forceinline__ uint64_t slab_members(const Row<VEC>& row, const FastMass& fm, int at,
+                                                 int part, const float (&v)[4], const Bounds& bd,
+                                                 int lane, int cap, int* n_list, float* list_z,
+                                                 int* list_i) {
+  uint32_t mem = 0, lst = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    mem |= v[k] >= bd.z1 ? 1u << k : 0u;
+    lst |= v[k] >= bd.z0 ? 1u << k : 0u;
+  }
+  lst &= ~mem;
+  while (lst) {
+    const int k = __ffs(lst) - 1, pos = atomicAdd(n_list, 1);
+    lst &= lst - 1;
+    if (pos < cap) {
+      list_z[pos] = pick4(v, k);
+      list_i[pos] = at + row.offset(part, k, lane);
+    }
+  }
+  if (__any(__popc(mem) > 2)) {  // most of the slab
+    float w[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w[k] = mem >> k & 1 ? v[k] : -INFINITY;
+    return slab_mass_all(row, fm, w);
+  }
+  return slab_mass(row, fm, v, mem);
+}
+
+// LDS of the one-row work groups.
+struct RowShared {
+  uint64_t hist[kBins];
+  uint64_t list_q[kListCap];
+  float list_z[kListCap];
+  int list_i[kListCap];
+  uint64_t bmass[kMaxBlocks], bties[kMaxBlocks];
+  uint64_t wave_s[kWaves];
+  uint64_t small_q[64];
+  double table[16];
+  uint64_t sel_before, sel_total, kappa;
+  float red_f[kWaves];
+  int sel_rank, n_list, n_small, tie_cut;
+};
+
+// Thread t holds h, the mass of rank t.  Finds the first rank whose running
+// mass from `above` reaches t_p (t_p > above); sel_rank = -1 if none does.
+// sel_total is the sum of all ranks.
+__device__ __forceinline__ void select_rank(RowShared& sh, uint64_t h, uint64_t above,
+                                            uint64_t t_p) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const float* z = logits + (int64_t)blockIdx.x * V;
-  // Wave w owns the index range [w0, w1), read coalesced in blocks of
-  // kUnroll slabs of 64 (all loads of a block issued before any use); index
-  // order is (wave, block, slab, lane).  Out-of-range slots read as -inf.
-  const int span = ((V + kWaves * 64 - 1) / (kWaves * 64)) * 64;
-  const int w0 = min(V, wave * span), w1 = min(V, w0 + span);
-  auto load_block = [&](int base, float (&zv)[kUnroll]) {
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const int i = base + u * 64 + lane;
-      zv[u] = i < w1 ? z[i] : -INFINITY;
-    }
-  };
-
-  // The passes whose results are sums (max, histograms, tie counts) may see
-  // a wave's tokens in any order: with V % 4 == 0 (rows 16-byte aligned) they
-  // read 16 bytes per lane, four times the bytes in flight of the scalar
-  // blocks, which is what bounds one work group's pass over a long row.  Only
-  // the final walk needs index order and keeps the scalar blocks.
-  const bool vec4 = (V & 3) == 0;
-  auto for_each = [&](auto&& f) {
-    if (vec4) {
-      for (int base = w0; base < w1; base += 256 * kUnroll4) {
-        float4 zv[kUnroll4];
-#pragma unroll
-        for (int u = 0; u < kUnroll4; ++u) {
-          const int i = base + (u * 64 + lane) * 4;  // i < w1 implies i + 3 < w1
-          zv[u] = i < w1 ? *(const float4*)(z + i)
-                         : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-        }
-#pragma unroll
-        for (int u = 0; u < kUnroll4; ++u) {
-          f(zv[u].x);
-          f(zv[u].y);
-          f(zv[u].z);
-          f(zv[u].w);
-        }
-      }
-    } else {
-      for (int base = w0; base < w1; base += 64 * kUnroll) {
-        float zv[kUnroll];
-        load_block(base, zv);
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) f(zv[u]);
-      }
-    }
-  };
-
-  // Row max.
-  float mx = -INFINITY;
-  for_each([&](float v) { mx = fmaxf(mx, v); });
-  mx = wave_max(mx);
-  if (lane == 0) red_f[wave] = mx;
+  const uint64_t incl = wave_scan_incl(h, lane);
   __syncthreads();
-  if (t == 0) {
-    float bmax = red_f[0];
-    for (int w = 1; w < kWaves; ++w) bmax = fmaxf(bmax, red_f[w]);
-    red_f[0] = bmax;
-  }
+  if (lane == 63) sh.wave_s[wave] = incl;
+  if (t == 0) sh.sel_rank = -1;
   __syncthreads();
-  const double m = (double)red_f[0];
-
-  // Radix select of the threshold key kappa: the largest key with
-  // mass{q >= kappa} >= T_p, where T_p = ceil(p24 * S / 2^24).  Each thread
-  // adds runs of equal digits in a register and flushes a run to the LDS
-  // histogram only when the digit changes: most tokens share one bin, and
-  // per-element atomics on one address would serialise.
-  uint64_t prefix = 0, above = 0, t_p = 0;
-  for (int r = 0; r < kRounds; ++r) {
-    const int shift = kShift[r], bins = 1 << kWidth[r];
-    for (int bin = t; bin < bins; bin += kThreads) hist[bin] = 0;
-    __syncthreads();
-    int run_bin = -1;
-    uint64_t run_sum = 0;
-    // keys of this round's range: [prefix << top, (prefix + 1) << top)
-    const int top = shift + kWidth[r];
-    const double xlo = x_floor(prefix << top), xhi = x_floor((prefix + 1) << top);
-    for_each([&](float zz) {
-      const double x = ((double)zz - m) * inv_t;
-      if (x < xlo || (r > 0 && x > xhi + 2e-9)) return;
-      const uint64_t q = mass_of(zz, m, inv_t);
-      if (q != 0 && (q >> top) == prefix) {
-        const int d = (int)((q >> shift) & (uint64_t)(bins - 1));
-        if (d != run_bin) {
-          if (run_bin >= 0) atomicAdd((unsigned long long*)&hist[run_bin], run_sum);
-          run_bin = d;
-          run_sum = 0;
-        }
-        run_sum += q;
-      }
-    });
-    if (run_bin >= 0) atomicAdd((unsigned long long*)&hist[run_bin], run_sum);
-    __syncthreads();
-    if (r == 0) {  // S = total mass, T_p from it
-      uint64_t part = 0;
-      for (int bin = t; bin < bins; bin += kThreads) part += hist[bin];
-      part = wave_sum_u64(part);
-      if (lane == 0) wave_a[wave] = part;
-      __syncthreads();
-      if (t == 0) {
-        uint64_t total = 0;
-        for (int w = 0; w < kWaves; ++w) total += wave_a[w];
-        sel[2] = (uint64_t)(((u128)p24 * total + ((u128)1 << 24) - 1) >> 24);
-      }
-      __syncthreads();
-    }
-    t_p = sel[2];
-    // Select the digit: walking bins from the top, the first whose
-    // cumulative mass (from `above`) reaches T_p.  Thread t holds the bins
-    // ranked 2t and 2t+1 from the top; a block scan gives the cumulative sums.
-    const int per = (bins + kThreads - 1) / kThreads;  // 2 or 1
-    uint64_t mine = 0;
-    for (int j = 0; j < per; ++j) {
-      const int rank = t * per + j;
-      if (rank < bins) mine += hist[bins - 1 - rank];
-    }
-    const uint64_t incl_w = wave_scan_incl(mine, lane);
-    if (lane == 63) wave_b[wave] = incl_w;
-    __syncthreads();
-    uint64_t before = above + incl_w - mine;
-    for (int w = 0; w < wave; ++w) before += wave_b[w];
-    for (int j = 0; j < per; ++j) {
-      const int rank = t * per + j;
-      if (rank >= bins) break;
-      const uint64_t h = hist[bins - 1 - rank];
-      // The digit is the first bin reaching T_p; the lowest bin (rank
-      // bins-1) always does, by the invariant mass(prefix range) >= T_p.
-      if (before < t_p && (before + h >= t_p || rank == bins - 1)) {
-        sel[0] = (uint64_t)(bins - 1 - rank);
-        sel[1] = before;
-      }
-      before += h;
-    }
-    __syncthreads();
-    prefix = (prefix << kWidth[r]) | sel[0];
-    above = sel[1];
-    __syncthreads();
-  }
-  const uint64_t kappa = prefix;  // >= 1: zero-mass keys never enter the histograms
-  // Tokens with q == kappa join the nucleus in index order until the mass
-  // reaches T_p: the first n_tie of them.
-  const uint64_t n_tie = (t_p - above + kappa - 1) / kappa;
-
-  // One pass: ties and strict-member mass per wave (only x >= x_floor(kappa)
-  // can reach kappa).
-  const double xk = x_floor(kappa);
-  uint64_t ties = 0, strict = 0;
-  for_each([&](float zz) {
-    if (((double)zz - m) * inv_t < xk) return;
-    const uint64_t q = mass_of(zz, m, inv_t);
-    ties += q == kappa;
-    strict += q > kappa ? q : 0;
-  });
-  ties = wave_sum_u64(ties);
-  strict = wave_sum_u64(strict);
-  if (lane == 0) {
-    wave_a[wave] = ties;
-    wave_b[wave] = strict;
-  }
-  __syncthreads();
-  // Wave w holds ties ranked [tie_base, tie_base + ties); its member ties
-  // are those ranked below n_tie.
-  uint64_t tie_base = 0, mass_base = 0, Z = 0, own = 0, tb = 0;
+  uint64_t before = above + incl - h, total = 0;
+#pragma unroll
   for (int w = 0; w < kWaves; ++w) {
-    const uint64_t nt = wave_a[w];
-    const uint64_t member_ties = n_tie > tb ? min(nt, n_tie - tb) : 0;
-    const uint64_t wm = wave_b[w] + member_ties * kappa;
-    if (w < wave) mass_base += wm;
-    if (w == wave) {
-      own = wm;
-      tie_base = tb;
-    }
-    Z += wm;
-    tb += nt;
+    if (w < wave) before += sh.wave_s[w];
+    total += sh.wave_s[w];
   }
-  float u = uniforms[blockIdx.x];
-  u = fminf(fmaxf(u, 0.f), 0x1.fffffep-1f);
-  const uint64_t u24 = (uint64_t)(u * 0x1p24f);
-  const uint64_t target = (uint64_t)(((u128)u24 * Z) >> 24);
-  // The wave whose nucleus mass range [mass_base, mass_base + own) holds
-  // target walks its range in index order.
-  if (own > 0 && mass_base <= target && target < mass_base + own) {
-    uint64_t run = mass_base, rank = tie_base;
-    bool found = false;
-    for (int base = w0; base < w1 && !found; base += 64 * kUnroll) {
-      float zv[kUnroll];
-      load_block(base, zv);
-#pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        const int i = base + u * 64 + lane;
-        uint64_t q = 0;
-        if (((double)zv[u] - m) * inv_t >= xk) q = mass_of(zv[u], m, inv_t);
-        const bool tie = q == kappa;  // out-of-range slots have q = 0 < kappa
-        const uint64_t tie_mask = __ballot(tie);
-        const uint64_t my_rank = rank + __popcll(tie_mask & ((1ull << lane) - 1));
-        const uint64_t mass = (q > kappa || (tie && my_rank < n_tie)) ? q : 0;
-        const uint64_t incl = run + wave_scan_incl(mass, lane);
-        const uint64_t hit = __ballot(mass > 0 && incl > target);
-        if (hit) {
-          if (lane == __ffsll((unsigned long long)hit) - 1) tokens[blockIdx.x] = i;
-          found = true;
-          break;
-        }
-        run = __shfl(incl, 63, 64);
-        rank += __popcll(tie_mask);
-      }
-    }
+  if (before < t_p && before + h >= t_p) {
+    sh.sel_rank = t;
+    sh.sel_before = before;
   }
+  if (t == 0) sh.sel_total = total;
+  __syncthreads();
 }
 
-// ---------------------------------------------------------------------------
-// Split form for batches below the CU count.  One work group per row leaves
-// most CUs idle and each pass over a 513 KB row runs at one CU's bandwidth;
-// here every pass is spread over C work groups per row, each owning a
-// contiguous chunk of the row, and the per-row decisions run in small
-// one-group kernels between them:
-//   chunk_max -> (chunk_hist(r) -> select(r)) x 4 -> chunk_ties -> walk.
-// All cross-chunk results are integer sums (or a max), so the token is the
-// one-group form's.  Workspace per row: the row state, C chunk maxima, C
-// partial histograms of 2048 bins and C (ties, strict mass) pairs.
-// ---------------------------------------------------------------------------
-constexpr int kST = 256, kSW = kST / 64;  // threads / waves of the split kernels
-
-// Per row, after the rounds so far: the key prefix, the mass of keys above
-// its range, and T_p.
-struct RowState {
-  uint64_t prefix, above, t_p;
-};
-
-struct SplitWs {
-  RowState* st;       // [B]
-  float* cmax;        // [B][C]
-  uint64_t* hist;     // [B][C][kMaxBins]
-  uint64_t* ties;     // [B][C][2]: tie count, strict-member mass
-};
-
-// Chunk c of a row: [i0, i1), the chunk length a multiple of 4 so that with
-// V % 4 == 0 every chunk start is 16-byte aligned.
-__device__ __forceinline__ void chunk_range(int V, int C, int c, int& i0, int& i1) {
-  const int span = (((V + C - 1) / C) + 3) & ~3;
-  i0 = min(V, c * span);
-  i1 = min(V, i0 + span);
-}
-
-// Calls f(z) for every token of [i0, i1) in some order, 16-byte loads when
-// the row length allows.
-template <typename F>
-__device__ __forceinline__ void chunk_for_each(const float* z, int V, int i0, int i1, F&& f) {
-  const int t = threadIdx.x;
-  if ((V & 3) == 0) {
-    for (int base = i0 + 4 * t; base < i1; base += 4 * kST * kUnroll4) {
-      float4 zv[kUnroll4];
-#pragma unroll
-      for (int u = 0; u < kUnroll4; ++u) {
-        const int i = base + 4 * kST * u;  // i < i1 implies i + 3 < i1
-        zv[u] = i < i1 ? *(const float4*)(z + i)
-                       : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-      }
-#pragma unroll
-      for (int u = 0; u < kUnroll4; ++u) {
-        f(zv[u].x);
-        f(zv[u].y);
-        f(zv[u].z);
-        f(zv[u].w);
-      }
-    }
-  } else {
-    for (int i = i0 + t; i < i1; i += kST) f(z[i]);
-  }
-}
-
-__device__ __forceinline__ uint64_t block_sum_u64(uint64_t v, uint64_t* red) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+__device__ __forceinline__ uint64_t group_sum_u64(RowShared& sh, uint64_t v) {
   v = wave_sum_u64(v);
   __syncthreads();
-  if (lane == 0) red[wave] = v;
+  if ((threadIdx.x & 63) == 0) sh.wave_s[threadIdx.x >> 6] = v;
   __syncthreads();
   uint64_t total = 0;
-  for (int w = 0; w < kSW; ++w) total += red[w];
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) total += sh.wave_s[w];
   return total;
 }
 
-__global__ __launch_bounds__(kST) void split_chunk_max(int V, int C, const float* __restrict__ logits,
-                                                       SplitWs ws) {
+// What the last steps need to know of the nucleus: its keys are q > kappa,
+// and q == kappa up to token tie_cut.
+struct Nucleus {
+  uint64_t kappa;
+  int tie_cut;
+};
+
+// The largest key whose mass from `above` reaches t_p, by radix select over the
+// keys that each(f) enumerates (f(q), any split over the threads): digits of
+// 10 bits, five rounds.  lo/hi(prefix range) let each() skip tokens.  Returns
+// kappa; sh.sel_before holds the mass above it.
+template <typename Each>
+__device__ uint64_t radix_key(RowShared& sh, uint64_t above, uint64_t t_p, Each&& each) {
+  uint64_t prefix = 0;
+  for (int r = 0; r < 5; ++r) {
+    const int shift = r < 4 ? 31 - 10 * r : 0, width = r < 4 ? 10 : 1;  // bits 40..31, .., 10..1, 0
+    __syncthreads();
+    sh.hist[threadIdx.x] = 0;
+    __syncthreads();
+    const int top = shift + width;
+    each(prefix << top, (prefix + 1) << top, [&](uint64_t q) {
+      if (q != 0 && (q >> top) == prefix)
+        atomicAdd((unsigned long long*)&sh.hist[(q >> shift) & ((1u << width) - 1)], q);
+    });
+    __syncthreads();
+    const int bins = 1 << width, rank = threadIdx.x;
+    select_rank(sh, rank < bins ? sh.hist[bins - 1 - rank] : 0, above, t_p);
+    prefix = (prefix << width) | (uint64_t)(bins - 1 - sh.sel_rank);
+    above = sh.sel_before;
+  }
+  return prefix;
+}
+
+// Walks tokens [at, at + n) in index order with weight w(token, q); returns
+// the first token whose running weight from `before` reaches `need`, or -1.
+template <bool VEC, typename W>
+__device__ int walk(RowShared& sh, const Row<VEC>& row, int at, int n, uint64_t before, uint64_t need,
+                    W&& w) {
+  for (int o = 0; o < n; o += kThreads) {
+    const int i = at + o + threadIdx.x;
+    uint64_t h = 0;
+    if (o + (int)threadIdx.x < n) h = w(i, mass_at(row.x(row.z[i])));
+    select_rank(sh, h, before, need);
+    const int found = sh.sel_rank;
+    before += sh.sel_total;
+    if (found >= 0) return at + o + found;
+  }
+  return -1;
+}
+
+// The radix path for a row whose threshold bin does not fit the list: kappa
+// over the whole row, then strict masses and ties per block.
+template <bool VEC>
+__device__ Nucleus radix_threshold(RowShared& sh, const Row<VEC>& row, uint64_t t_p) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint64_t kappa = radix_key(sh, 0, t_p, [&](uint64_t lo, uint64_t hi, auto&& f) {
+    const double xlo = x_floor(lo), xhi = x_floor(hi) + 2e-9;
+#pragma unroll 1
+    for (int64_t i = threadIdx.x; i < row.V; i += kThreads) {
+      const double x = row.x(row.z[i]);
+      if (x >= xlo && x <= xhi) f(mass_at(x));
+    }
+  });
+  const uint64_t above = sh.sel_before;
+  const uint64_t n_tie = (t_p - above + kappa - 1) / kappa;
+  const double xk = x_floor(kappa);
+#pragma unroll 1
+  for (int b = wave; b < row.nb; b += kWaves) {
+    uint64_t strict = 0, ties = 0;
+    const int at = b * row.blen, n = min(row.blen, row.V - at);
+#pragma unroll 1
+    for (int o = lane; o < n; o += 64) {
+      const double x = row.x(row.z[at + o]);
+      if (!(x >= xk)) continue;
+      const uint64_t q = mass_at(x);
+      strict += q > kappa ? q : 0;
+      ties += q == kappa;
+    }
+    strict = wave_sum_u64(strict);
+    ties = wave_sum_u64(ties);
+    if (lane == 0) {
+      sh.bmass[b] = strict;
+      sh.bties[b] = ties;
+    }
+  }
+  __syncthreads();
+  // The block that holds the last member tie, and that tie's index.
+  const int t = threadIdx.x;
+  select_rank(sh, t < row.nb ? sh.bties[t] : 0, 0, n_tie);
+  const int tb = sh.sel_rank;
+  const uint64_t tie0 = sh.sel_before;
+  if (t < row.nb) {
+    const uint64_t members = t < tb ? sh.bties[t] : t == tb ? n_tie - tie0 : 0;
+    sh.bmass[t] += members * kappa;
+  }
+  const int at = tb * row.blen;
+  const int cut = walk(sh, row, at, min(row.blen, row.V - at), tie0, n_tie,
+                       [&](int, uint64_t q) -> uint64_t { return q == kappa; });
+  return {kappa, cut};
+}
+
+// Step 4: kappa, ties and the blocks' nucleus masses from the list (n entries
+// of [z0, z1); bmass holds the masses at or above z1).
+template <bool VEC>
+__device__ Nucleus list_threshold(RowShared& sh, const Row<VEC>& row, const Bounds& bd, int n,
+                                  uint64_t t_p) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const uint64_t above1 = group_sum_u64(sh, t < row.nb ? sh.bmass[t] : 0);
+  const double x1 = row.x(bd.z1), scale = (double)kBins / (x1 - row.x(bd.z0));
+  auto sub_bin = [&](float z) { return min(kBins - 1, max(0, (int)((x1 - row.x(z)) * scale))); };
+  sh.hist[t] = 0;
+  if (t == 0) sh.n_small = 0;
+  __syncthreads();
+  for (int e = t; e < n; e += kThreads) {
+    const uint64_t q = mass_at(row.x(sh.list_z[e]));
+    sh.list_q[e] = q;
+    if (q) atomicAdd((unsigned long long*)&sh.hist[sub_bin(sh.list_z[e])], q);
+  }
+  __syncthreads();
+  select_rank(sh, sh.hist[t], above1, t_p);
+  const int sub = sh.sel_rank;
+  const uint64_t above_s = sh.sel_before;
+  for (int e = t; e < n; e += kThreads)
+    if (sub_bin(sh.list_z[e]) == sub) {
+      const int p = atomicAdd(&sh.n_small, 1);
+      if (p < 64) sh.small_q[p] = sh.list_q[e];
+    }
+  __syncthreads();
+  const int ns = sh.n_small;
+  uint64_t kappa;
+  if (ns <= 64) {
+    if (wave == 0) {
+      const uint64_t q = lane < ns ? sh.small_q[lane] : 0;
+      uint64_t gt = above_s, eq = 0;
+      for (int j = 0; j < ns; ++j) {
+        const uint64_t o = lane_u64(q, j);
+        gt += o > q ? o : 0;
+        eq += o == q ? o : 0;
+      }
+      if (q && gt < t_p && gt + eq >= t_p) sh.kappa = q;
+    }
+    __syncthreads();
+    kappa = sh.kappa;
+  } else {
+    kappa = radix_key(sh, above1, t_p, [&](uint64_t, uint64_t, auto&& f) {
+      for (int e = t; e < n; e += kThreads) f(sh.list_q[e]);
+    });
+  }
+  uint64_t strict = 0, ties = 0;
+  for (int e = t; e < n; e += kThreads) {
+    const uint64_t q = sh.list_q[e];
+    strict += q > kappa ? q : 0;
+    ties += q == kappa;
+  }
+  const uint64_t above = above1 + group_sum_u64(sh, strict);
+  ties = group_sum_u64(sh, ties);
+  const uint64_t n_tie = (t_p - above + kappa - 1) / kappa;
+  if (t == 0) sh.tie_cut = INT_MAX;
+  __syncthreads();
+  if (n_tie < ties) {  // ties join in index order: the last member's index
+    for (int e = t; e < n; e += kThreads) {
+      if (sh.list_q[e] != kappa) continue;
+      const int i = sh.list_i[e];
+      uint64_t rank = 0;
+      for (int j = 0; j < n; ++j) rank += sh.list_q[j] == kappa && sh.list_i[j] < i;
+      if (rank == n_tie - 1) sh.tie_cut = i;
+    }
+    __syncthreads();
+  }
+  const int cut = sh.tie_cut;
+  for (int e = t; e < n; e += kThreads) {
+    const uint64_t q = sh.list_q[e];
+    if (q > kappa || (q == kappa && sh.list_i[e] <= cut))
+      atomicAdd((unsigned long long*)&sh.bmass[sh.list_i[e] / row.blen], q);
+  }
+  __syncthreads();
+  return {kappa, cut};
+}
+
+// Step 5: the block that holds the target, then its token.
+template <bool VEC>
+__device__ void take_token(RowShared& sh, const Row<VEC>& row, const Nucleus& nu, float u,
+                           int32_t* token) {
+  const int t = threadIdx.x;
+  const uint64_t Z = group_sum_u64(sh, t < row.nb ? sh.bmass[t] : 0);
+  u = fminf(fmaxf(u, 0.f), 0x1.fffffep-1f);
+  const uint64_t u24 = (uint64_t)(u * 0x1p24f);
+  const uint64_t target = (uint64_t)(((u128)u24 * Z) >> 24);
+  select_rank(sh, t < row.nb ? sh.bmass[t] : 0, 0, target + 1);
+  const int b = sh.sel_rank;
+  if (b < 0) return;  // no mass at all (a row without finite logits): no token
+  const uint64_t before = sh.sel_before;
+  const int at = b * row.blen;
+  const int i = walk(sh, row, at, min(row.blen, row.V - at), before, target + 1,
+                     [&](int tok, uint64_t q) -> uint64_t {
+                       return q > nu.kappa || (q == nu.kappa && tok <= nu.tie_cut) ? q : 0;
+                     });
+  if (t == 0 && i >= 0) *token = i;
+}
+
+__device__ __forceinline__ uint64_t threshold_mass(uint32_t p24, uint64_t S) {
+  return (uint64_t)(((u128)p24 * S + ((u128)1 << 24) - 1) >> 24);
+}
+
+// Steps 2 to 5 of one row by one work group of kThreads.
+template <bool VEC>
+__device__ void sample_row(RowShared& sh, const Row<VEC>& row, uint32_t p24, float u, int32_t* token) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const FastMass fm = make_fast(row.m, row.inv_t, sh.table);
+  fill_table(sh.table);
+  if (t == 0) sh.n_list = 0;
+  sh.hist[t] = 0;
+  __syncthreads();
+  uint64_t sum = 0;
+  auto end_block = [&](int b) {
+    sum = wave_sum_u64(sum);
+    if (lane == 0) sh.bmass[b] = sum;
+    sum = 0;
+  };
+  if (p24 == 1u << 24) {  // every token of nonzero mass
+    row.slabs(wave, row.nb, kWaves, lane, [&](int b, int, int, const float(&v)[4], bool end) {
+      sum += slab_mass_all(row, fm, v);
+      if (end) end_block(b);
+    });
+    __syncthreads();
+    take_token(sh, row, {0, INT_MAX}, u, token);
+    return;
+  }
+  row.slabs(wave, row.nb, kWaves, lane,
+            [&](int, int, int, const float(&v)[4], bool) { slab_hist(row, fm, v, sh.hist); });
+  __syncthreads();
+  const uint64_t S = group_sum_u64(sh, sh.hist[t]);
+  if (S == 0) return;  // a row without finite logits
+  const uint64_t t_p = threshold_mass(p24, S);
+  select_rank(sh, sh.hist[t], 0, t_p);
+  const int bin = sh.sel_rank;
+  const Bounds bd = bin_bounds(row, bin);
+  bool listed = !bin_deep(bin);
+  if (listed) {
+    row.slabs(wave, row.nb, kWaves, lane, [&](int b, int at, int part, const float(&v)[4], bool end) {
+      sum += slab_members(row, fm, at, part, v, bd, lane, kListCap, &sh.n_list, sh.list_z, sh.list_i);
+      if (end) end_block(b);
+    });
+    __syncthreads();
+    listed = sh.n_list <= kListCap;
+  }
+  const Nucleus nu = listed ? list_threshold(sh, row, bd, sh.n_list, t_p)
+                            : radix_threshold(sh, row, t_p);
+  take_token(sh, row, nu, u, token);
+}
+
+// Row maximum by a work group of kThreads: eight 16-byte loads in flight per lane.
+template <bool VEC>
+__device__ float row_max_group(RowShared& sh, const Row<VEC>& row) {
+  const int t = threadIdx.x;
+  float mx = -INFINITY;
+  if constexpr (VEC) {
+    const int n4 = row.V / 4;
+    for (int base = 0; base < n4; base += 8 * kThreads) {
+      float4 f[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) f[u] = ((const float4*)row.z)[min(base + u * kThreads + t, n4 - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        mx = fmaxf(mx, fmaxf(fmaxf(f[u].x, f[u].y), fmaxf(f[u].z, f[u].w)));
+    }
+  } else {
+    for (int64_t base = 0; base < row.V; base += 8 * kThreads) {
+      float f[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        f[u] = row.z[min(base + u * kThreads + t, (int64_t)row.V - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) mx = fmaxf(mx, f[u]);
+    }
+  }
+  mx = wave_max(mx);
+  if ((t & 63) == 0) sh.red_f[t >> 6] = mx;
+  __syncthreads();
+  mx = sh.red_f[0];
+#pragma unroll
+  for (int w = 1; w < kWaves; ++w) mx = fmaxf(mx, sh.red_f[w]);
+  return mx;
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(kThreads) void sample_top_p_kernel(
+    int V, const float* __restrict__ logits, double inv_t, uint32_t p24,
+    const float* __restrict__ uniforms, int32_t* __restrict__ tokens) {
+  __shared__ RowShared sh;
+  const int b = blockIdx.x;
+  Row<VEC> row = make_row<VEC>(V, logits, b, inv_t);
+  row.m = (double)row_max_group(sh, row);
+  sample_row(sh, row, p24, uniforms[b], tokens + b);
+}
+
+// ---------------------------------------------------------------------------
+// Split form for small batches.  One work group per row leaves most CUs idle
+// and each pass over a 513 KB row runs at one CU's rate; here the three passes
+// over the row are spread over C work groups per row, each owning a run of the
+// row's index blocks, and steps 2's decision and 4 to 5 run on one group per
+// row between and after them:
+//   split_max -> split_hist -> split_bin -> split_members -> split_finish
+// (without the histogram and its decision when top_p = 1).  All cross-chunk
+// results are integer sums, maxima and an unordered list, so the token is the
+// one-group form's.
+// ---------------------------------------------------------------------------
+constexpr int kST = 512, kSW = kST / 64;  // threads / waves of the chunk kernels
+
+struct RowState {
+  uint64_t t_p;
+  int32_t bin;   // threshold bin; -1: no mass in the row
+  int32_t deep;  // the row takes the radix path
+};
+
+struct SplitWs {
+  RowState* st;    // [B]
+  float* cmax;     // [B][C]
+  uint64_t* hist;  // [B][C][kBins]
+  uint64_t* bmass; // [B][kMaxBlocks]
+  int* count;      // [B][C] listed tokens of a chunk (may pass cap)
+  float* list_z;   // [B][C][cap]
+  int* list_i;     // [B][C][cap]
+  int C, cap;
+};
+
+// Blocks of chunk c: [b0, b1).
+__device__ __forceinline__ void chunk_blocks(int nb, int C, int c, int& b0, int& b1) {
+  const int per = (nb + C - 1) / C;
+  b0 = min(nb, c * per);
+  b1 = min(nb, b0 + per);
+}
+
+// Row max from the chunk maxima (the same float max as one pass); C <= 64.
+__device__ __forceinline__ double split_row_max(const SplitWs& ws, int b) {
+  const int lane = threadIdx.x & 63;
+  const float v = lane < ws.C ? ws.cmax[(int64_t)b * ws.C + lane] : -INFINITY;
+  return (double)wave_max(v);
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(kST) void split_max(int V, const float* __restrict__ logits,
+                                                 SplitWs ws) {
   __shared__ float red[kSW];
   const int c = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int i0, i1;
-  chunk_range(V, C, c, i0, i1);
+  const Row<VEC> row = make_row<VEC>(V, logits, b, 1.0);
+  int b0, b1;
+  chunk_blocks(row.nb, ws.C, c, b0, b1);
   float mx = -INFINITY;
-  chunk_for_each(logits + (int64_t)b * V, V, i0, i1, [&](float v) { mx = fmaxf(mx, v); });
+  row.slabs(b0 + wave, b1, kSW, lane, [&](int, int, int, const float(&v)[4], bool) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) mx = fmaxf(mx, v[i]);
+  });
   mx = wave_max(mx);
   if (lane == 0) red[wave] = mx;
   __syncthreads();
   if (threadIdx.x == 0) {
-    float bm = red[0];
-    for (int w = 1; w < kSW; ++w) bm = fmaxf(bm, red[w]);
-    ws.cmax[(int64_t)b * C + c] = bm;
+    for (int w = 1; w < kSW; ++w) mx = fmaxf(mx, red[w]);
+    ws.cmax[(int64_t)b * ws.C + c] = mx;
   }
 }
 
-// Row max from the chunk maxima (the same float max as one pass).
-__device__ __forceinline__ double row_max(const SplitWs& ws, int b, int C) {
-  float m = -INFINITY;
-  for (int c = 0; c < C; ++c) m = fmaxf(m, ws.cmax[(int64_t)b * C + c]);
-  return (double)m;
+template <bool VEC>
+__global__ __launch_bounds__(kST) void split_hist(int V, const float* __restrict__ logits,
+                                                  double inv_t, SplitWs ws) {
+  __shared__ uint64_t hist[kBins];
+  __shared__ double table[16];
+  const int c = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  Row<VEC> row = make_row<VEC>(V, logits, b, inv_t);
+  row.m = split_row_max(ws, b);
+  const FastMass fm = make_fast(row.m, inv_t, table);
+  fill_table(table);
+  for (int i = threadIdx.x; i < kBins; i += kST) hist[i] = 0;
+  __syncthreads();
+  int b0, b1;
+  chunk_blocks(row.nb, ws.C, c, b0, b1);
+  row.slabs(b0 + wave, b1, kSW, lane,
+            [&](int, int, int, const float(&v)[4], bool) { slab_hist(row, fm, v, hist); });
+  __syncthreads();
+  uint64_t* dst = ws.hist + ((int64_t)b * ws.C + c) * kBins;
+  for (int i = threadIdx.x; i < kBins; i += kST) dst[i] = hist[i];
 }
 
-// Round r's histogram of one chunk: the tokens whose key lies in the
-// current prefix range, by their round-r digit, as in the one-group form.
-__global__ __launch_bounds__(kST) void split_chunk_hist(int V, int C, int r,
-                                                        const float* __restrict__ logits,
-                                                        double inv_t, SplitWs ws) {
-  __shared__ uint64_t hist[kMaxBins];
-  const int c = blockIdx.x, b = blockIdx.y;
-  const int shift = kShift[r], bins = 1 << kWidth[r], top = shift + kWidth[r];
-  const double m = row_max(ws, b, C);
-  const uint64_t prefix = r ? ws.st[b].prefix : 0;
-  for (int bin = threadIdx.x; bin < bins; bin += kST) hist[bin] = 0;
-  __syncthreads();
-  const double xlo = x_floor(prefix << top), xhi = x_floor((prefix + 1) << top);
-  int i0, i1;
-  chunk_range(V, C, c, i0, i1);
-  int run_bin = -1;
-  uint64_t run_sum = 0;
-  chunk_for_each(logits + (int64_t)b * V, V, i0, i1, [&](float zz) {
-    const double x = ((double)zz - m) * inv_t;
-    if (x < xlo || (r > 0 && x > xhi + 2e-9)) return;
-    const uint64_t q = mass_of(zz, m, inv_t);
-    if (q != 0 && (q >> top) == prefix) {
-      const int d = (int)((q >> shift) & (uint64_t)(bins - 1));
-      if (d != run_bin) {
-        if (run_bin >= 0) atomicAdd((unsigned long long*)&hist[run_bin], run_sum);
-        run_bin = d;
-        run_sum = 0;
-      }
-      run_sum += q;
-    }
-  });
-  if (run_bin >= 0) atomicAdd((unsigned long long*)&hist[run_bin], run_sum);
-  __syncthreads();
-  uint64_t* dst = ws.hist + ((int64_t)b * C + c) * kMaxBins;
-  for (int bin = threadIdx.x; bin < bins; bin += kST) dst[bin] = hist[bin];
+__global__ __launch_bounds__(kThreads) void split_bin(uint32_t p24, SplitWs ws) {
+  __shared__ RowShared sh;
+  const int b = blockIdx.x, t = threadIdx.x;
+  const uint64_t* h0 = ws.hist + (int64_t)b * ws.C * kBins + t;
+  uint64_t h = 0;
+  for (int c0 = 0; c0 < ws.C; c0 += 8) {  // C is a multiple of 8
+    uint64_t v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = h0[(int64_t)(c0 + u) * kBins];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) h += v[u];
+  }
+  const uint64_t S = group_sum_u64(sh, h);
+  RowState st{0, -1, 0};
+  if (S != 0) {
+    st.t_p = threshold_mass(p24, S);
+    select_rank(sh, h, 0, st.t_p);
+    st.bin = sh.sel_rank;
+    st.deep = bin_deep(st.bin);
+  }
+  if (t == 0) ws.st[b] = st;
 }
 
-// Round r's decision for one row: sum the chunk histograms, then pick the
-// digit exactly as the one-group form (walking bins from the top, the first
-// whose cumulative mass from `above` reaches T_p).
-__global__ __launch_bounds__(kThreads) void split_select(int C, int r, uint32_t p24,
-                                                         SplitWs ws) {
-  __shared__ uint64_t hist[kMaxBins];
-  __shared__ uint64_t wave_a[kWaves], wave_b[kWaves];
-  __shared__ uint64_t sel[2];
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, b = blockIdx.x;
-  const int bins = 1 << kWidth[r];
-  const uint64_t* h0 = ws.hist + (int64_t)b * C * kMaxBins;
-  for (int bin = t; bin < bins; bin += kThreads) {
-    uint64_t v = 0;
-    for (int c = 0; c < C; ++c) v += h0[(int64_t)c * kMaxBins + bin];
-    hist[bin] = v;
-  }
+template <bool VEC>
+__global__ __launch_bounds__(kST) void split_members(int V, const float* __restrict__ logits,
+                                                     double inv_t, int all, SplitWs ws) {
+  __shared__ int n_list;
+  __shared__ double table[16];
+  const int c = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  Row<VEC> row = make_row<VEC>(V, logits, b, inv_t);
+  row.m = split_row_max(ws, b);
+  int b0, b1;
+  chunk_blocks(row.nb, ws.C, c, b0, b1);
+  uint64_t* bmass = ws.bmass + (int64_t)b * kMaxBlocks;
+  const FastMass fm = make_fast(row.m, inv_t, table);
+  fill_table(table);
+  if (threadIdx.x == 0) n_list = 0;
   __syncthreads();
-  RowState st = ws.st[b];
-  if (r == 0) {
-    st.prefix = 0;
-    st.above = 0;
-    uint64_t part = 0;
-    for (int bin = t; bin < bins; bin += kThreads) part += hist[bin];
-    part = wave_sum_u64(part);
-    if (lane == 0) wave_a[wave] = part;
-    __syncthreads();
-    uint64_t total = 0;
-    for (int w = 0; w < kWaves; ++w) total += wave_a[w];
-    st.t_p = (uint64_t)(((u128)p24 * total + ((u128)1 << 24) - 1) >> 24);
+  uint64_t sum = 0;
+  auto end_block = [&](int k) {
+    sum = wave_sum_u64(sum);
+    if (lane == 0) bmass[k] = sum;
+    sum = 0;
+  };
+  if (all) {  // top_p = 1
+    row.slabs(b0 + wave, b1, kSW, lane, [&](int k, int, int, const float(&v)[4], bool end) {
+      sum += slab_mass_all(row, fm, v);
+      if (end) end_block(k);
+    });
+    return;
   }
-  const int per = (bins + kThreads - 1) / kThreads;
-  uint64_t mine = 0;
-  for (int j = 0; j < per; ++j) {
-    const int rank = t * per + j;
-    if (rank < bins) mine += hist[bins - 1 - rank];
-  }
-  const uint64_t incl_w = wave_scan_incl(mine, lane);
-  if (lane == 63) wave_b[wave] = incl_w;
-  __syncthreads();
-  uint64_t before = st.above + incl_w - mine;
-  for (int w = 0; w < wave; ++w) before += wave_b[w];
-  for (int j = 0; j < per; ++j) {
-    const int rank = t * per + j;
-    if (rank >= bins) break;
-    const uint64_t h = hist[bins - 1 - rank];
-    if (before < st.t_p && (before + h >= st.t_p || rank == bins - 1)) {
-      sel[0] = (uint64_t)(bins - 1 - rank);
-      sel[1] = before;
-    }
-    before += h;
-  }
-  __syncthreads();
-  if (t == 0) {
-    st.prefix = (st.prefix << kWidth[r]) | sel[0];
-    st.above = sel[1];
-    ws.st[b] = st;
-  }
-}
-
-// Per chunk: the number of keys equal to kappa and the mass of keys above it.
-__global__ __launch_bounds__(kST) void split_chunk_ties(int V, int C,
-                                                        const float* __restrict__ logits,
-                                                        double inv_t, SplitWs ws) {
-  __shared__ uint64_t red[kSW];
-  const int c = blockIdx.x, b = blockIdx.y;
-  const double m = row_max(ws, b, C);
-  const uint64_t kappa = ws.st[b].prefix;
-  const double xk = x_floor(kappa);
-  int i0, i1;
-  chunk_range(V, C, c, i0, i1);
-  uint64_t ties = 0, strict = 0;
-  chunk_for_each(logits + (int64_t)b * V, V, i0, i1, [&](float zz) {
-    if (((double)zz - m) * inv_t < xk) return;
-    const uint64_t q = mass_of(zz, m, inv_t);
-    ties += q == kappa;
-    strict += q > kappa ? q : 0;
-  });
-  ties = block_sum_u64(ties, red);
-  strict = block_sum_u64(strict, red);
-  if (threadIdx.x == 0) {
-    ws.ties[((int64_t)b * C + c) * 2] = ties;
-    ws.ties[((int64_t)b * C + c) * 2 + 1] = strict;
-  }
-}
-
-// The row's token: the chunk whose nucleus mass range holds the target is
-// walked in index order, 256 tokens at a time, with a work-group scan.
-__global__ __launch_bounds__(kST) void split_walk(int V, int C, const float* __restrict__ logits,
-                                                  double inv_t,
-                                                  const float* __restrict__ uniforms,
-                                                  int32_t* __restrict__ tokens, SplitWs ws) {
-  __shared__ uint64_t wsum[kSW], wtie[kSW];
-  __shared__ int found_at;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, b = blockIdx.x;
   const RowState st = ws.st[b];
-  const uint64_t kappa = st.prefix;
-  const uint64_t n_tie = (st.t_p - st.above + kappa - 1) / kappa;
-  const uint64_t* tc = ws.ties + (int64_t)b * C * 2;
-  // Nucleus mass of every chunk (its strict members plus its member ties,
-  // ties ranked in index order across chunks).
-  uint64_t Z = 0, tb = 0;
-  for (int c = 0; c < C; ++c) {
-    const uint64_t nt = tc[2 * c];
-    const uint64_t mt = n_tie > tb ? min(nt, n_tie - tb) : 0;
-    Z += tc[2 * c + 1] + mt * kappa;
-    tb += nt;
+  if (st.bin < 0 || st.deep) return;  // uniform over the group
+  const Bounds bd = bin_bounds(row, st.bin);
+  const int64_t at0 = ((int64_t)b * ws.C + c) * ws.cap;
+  row.slabs(b0 + wave, b1, kSW, lane, [&](int k, int at, int part, const float(&v)[4], bool end) {
+    sum += slab_members(row, fm, at, part, v, bd, lane, ws.cap, &n_list, ws.list_z + at0,
+                        ws.list_i + at0);
+    if (end) end_block(k);
+  });
+  __syncthreads();
+  if (threadIdx.x == 0) ws.count[(int64_t)b * ws.C + c] = n_list;
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(kThreads) void split_finish(int V, const float* __restrict__ logits,
+                                                         double inv_t, int all,
+                                                         const float* __restrict__ uniforms,
+                                                         int32_t* __restrict__ tokens, SplitWs ws) {
+  __shared__ RowShared sh;
+  __shared__ int base[65];
+  const int b = blockIdx.x, t = threadIdx.x;
+  Row<VEC> row = make_row<VEC>(V, logits, b, inv_t);
+  row.m = split_row_max(ws, b);
+  Nucleus nu{0, INT_MAX};
+  if (all) {
+    if (t < row.nb) sh.bmass[t] = ws.bmass[(int64_t)b * kMaxBlocks + t];
+    __syncthreads();
+  } else {
+    const RowState st = ws.st[b];
+    if (st.bin < 0) return;  // a row without finite logits
+    bool listed = !st.deep;
+    if (listed) {
+      if (t == 0) {  // where each chunk's tokens start in the row's list
+        int n = 0;
+        bool fits = true;
+        for (int c = 0; c < ws.C; ++c) {
+          base[c] = n;
+          const int k = ws.count[(int64_t)b * ws.C + c];
+          fits = fits && k <= ws.cap;
+          n += min(k, ws.cap);
+        }
+        base[ws.C] = n;
+        sh.n_list = fits && n <= kListCap ? n : -1;
+      }
+      if (t < row.nb) sh.bmass[t] = ws.bmass[(int64_t)b * kMaxBlocks + t];
+      __syncthreads();
+      listed = sh.n_list >= 0;
+    }
+    if (listed) {
+      for (int c = t >> 6; c < ws.C; c += kWaves) {
+        const int64_t at0 = ((int64_t)b * ws.C + c) * ws.cap;
+        for (int e = t & 63; e < base[c + 1] - base[c]; e += 64) {
+          sh.list_z[base[c] + e] = ws.list_z[at0 + e];
+          sh.list_i[base[c] + e] = ws.list_i[at0 + e];
+        }
+      }
+      __syncthreads();
+      nu = list_threshold(sh, row, bin_bounds(row, st.bin), sh.n_list, st.t_p);
+    } else {
+      nu = radix_threshold(sh, row, st.t_p);
+    }
   }
-  float u = uniforms[b];
-  u = fminf(fmaxf(u, 0.f), 0x1.fffffep-1f);
-  const uint64_t u24 = (uint64_t)(u * 0x1p24f);
-  const uint64_t target = (uint64_t)(((u128)u24 * Z) >> 24);
-  uint64_t mass_base = 0, tie_base = 0;
-  int cs = -1;
-  tb = 0;
-  for (int c = 0; c < C; ++c) {
-    const uint64_t nt = tc[2 * c];
-    const uint64_t mt = n_tie > tb ? min(nt, n_tie - tb) : 0;
-    const uint64_t own = tc[2 * c + 1] + mt * kappa;
-    if (own > 0 && mass_base <= target && target < mass_base + own) {
-      cs = c;
-      tie_base = tb;
-      break;
-    }
-    mass_base += own;
-    tb += nt;
-  }
-  if (cs < 0) return;  // cannot happen: Z > 0 (the max token has mass 2^40)
-  const double m = row_max(ws, b, C);
-  const double xk = x_floor(kappa);
-  const float* z = logits + (int64_t)b * V;
-  int i0, i1;
-  chunk_range(V, C, cs, i0, i1);
-  if (t == 0) found_at = INT_MAX;
-  uint64_t run = mass_base, rank = tie_base;
-  for (int base = i0; base < i1; base += kST) {
-    const int i = base + t;
-    uint64_t q = 0;
-    if (i < i1) {
-      const float zz = z[i];
-      if (((double)zz - m) * inv_t >= xk) q = mass_of(zz, m, inv_t);
-    }
-    const bool tie = q == kappa;  // out-of-range slots have q = 0 < kappa
-    // Tie ranks and member masses in index order: wave scans, then the
-    // waves before this one.
-    const uint64_t tie_mask = __ballot(tie);
-    const uint64_t tie_before_w = __popcll(tie_mask & ((1ull << lane) - 1));
-    if (lane == 0) wtie[wave] = __popcll(tie_mask);
-    __syncthreads();
-    uint64_t tie_before = rank + tie_before_w;
-    for (int w = 0; w < wave; ++w) tie_before += wtie[w];
-    const uint64_t mass = (q > kappa || (tie && tie_before < n_tie)) ? q : 0;
-    const uint64_t incl_w = wave_scan_incl(mass, lane);
-    if (lane == 63) wsum[wave] = incl_w;
-    __syncthreads();
-    uint64_t incl = run + incl_w;
-    for (int w = 0; w < wave; ++w) incl += wsum[w];
-    // The first token (lowest index) whose running mass passes the target.
-    const uint64_t hit = __ballot(mass > 0 && incl > target);
-    if (hit && lane == __ffsll((unsigned long long)hit) - 1) atomicMin(&found_at, i);
-    __syncthreads();
-    if (found_at != INT_MAX) {
-      if (t == 0) tokens[b] = found_at;
-      return;  // uniform: found_at is shared
-    }
-    for (int w = 0; w < kSW; ++w) {
-      run += wsum[w];
-      rank += wtie[w];
-    }
-    __syncthreads();
-  }
+  take_token(sh, row, nu, uniforms[b], tokens + b);
 }
 
 }  // namespace
 
 namespace {
 
-constexpr int sample_split_chunks(int B) {
-  // About 256 work groups per pass: 16 chunks per row up to 16 rows, 8 up
-  // to 32, none above (at 64 rows the split form's eleven launches already
-  // cost more than its wider passes save).
-  return (B > 0 ? 256 / B : 1) >= 16 ? 16 : (B > 0 ? 256 / B : 1) >= 8 ? 8 : 1;
-}
+// Chunks per row: about 256 work groups per pass.  Above 32 rows one group per
+// row: the split form would need scratch that grows with the batch, and its
+// callers hold none there.
+constexpr int sample_split_chunks(int B) { return B <= 8 ? 32 : B <= 16 ? 16 : B <= 32 ? 8 : 1; }
+// Listed tokens a chunk may hold: 16 times what a Gaussian row of any
+// temperature puts into one bin of the histogram.
+constexpr int sample_list_cap(int C) { return C == 32 ? 512 : 1024; }
+
+constexpr int64_t al256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 
 constexpr int64_t split_workspace_bytes(int B) {
-  return sample_split_chunks(B) == 1
-             ? 0
-             : (int64_t)B * ((int64_t)sizeof(RowState) + sample_split_chunks(B) * 4 +
-                             (int64_t)sample_split_chunks(B) * kMaxBins * 8 +
-                             sample_split_chunks(B) * 16) +
-                   1024;
+  const int C = sample_split_chunks(B);
+  return C == 1 ? 0
+                : al256((int64_t)B * sizeof(RowState)) + al256((int64_t)B * C * 4) +
+                      al256((int64_t)B * C * kBins * 8) + al256((int64_t)B * kMaxBlocks * 8) +
+                      al256((int64_t)B * C * 4) + 2 * al256((int64_t)B * C * sample_list_cap(C) * 4) +
+                      256;
 }
 
 constexpr int64_t max_split_workspace_bytes() {
@@ -665,6 +990,24 @@ hipError_t sample_scratch_ptr(void** out) {
   return hipSuccess;
 }
 
+namespace {
+
+template <bool VEC>
+void launch_split(int B, int V, const float* logits, double inv_t, uint32_t p24,
+                  const float* uniforms, int32_t* tokens, const SplitWs& ws, hipStream_t stream) {
+  const dim3 grid(ws.C, B);
+  const int all = p24 == 1u << 24;
+  split_max<VEC><<<grid, kST, 0, stream>>>(V, logits, ws);
+  if (!all) {
+    split_hist<VEC><<<grid, kST, 0, stream>>>(V, logits, inv_t, ws);
+    split_bin<<<B, kThreads, 0, stream>>>(p24, ws);
+  }
+  split_members<VEC><<<grid, kST, 0, stream>>>(V, logits, inv_t, all, ws);
+  split_finish<VEC><<<B, kThreads, 0, stream>>>(V, logits, inv_t, all, uniforms, tokens, ws);
+}
+
+}  // namespace
+
 hipError_t launch_sample_top_p(int B, int V, const float* logits, float temperature, float top_p,
                                const float* uniforms, int32_t* tokens, void* workspace,
                                int64_t ws_bytes, hipStream_t stream) {
@@ -672,31 +1015,37 @@ hipError_t launch_sample_top_p(int B, int V, const float* logits, float temperat
   const double inv_t = 1.0 / (double)temperature;
   uint32_t p24 = (uint32_t)rint((double)top_p * 16777216.0);
   p24 = p24 < 1 ? 1 : (p24 > (1u << 24) ? (1u << 24) : p24);
+  // 16-byte loads need every row 16-byte aligned.
+  const bool vec = (V & 3) == 0 && ((uintptr_t)logits & 15) == 0;
   const int C = sample_split_chunks(B);
   if (C == 1 || !workspace || ws_bytes < sample_workspace_bytes(B)) {
-    sample_top_p_kernel<<<B, kThreads, 0, stream>>>(V, logits, inv_t, p24, uniforms, tokens);
+    if (vec)
+      sample_top_p_kernel<true><<<B, kThreads, 0, stream>>>(V, logits, inv_t, p24, uniforms, tokens);
+    else
+      sample_top_p_kernel<false><<<B, kThreads, 0, stream>>>(V, logits, inv_t, p24, uniforms, tokens);
     return hipGetLastError();
   }
-  // Workspace layout (256-byte aligned pieces): row states, chunk maxima,
-  // histograms, tie pairs.
-  auto al = [](int64_t x) { return (x + 255) & ~(int64_t)255; };
-  char* p = (char*)workspace;
+  // Workspace layout (256-byte aligned pieces, from an aligned start).
+  char* p = (char*)(((uintptr_t)workspace + 255) & ~(uintptr_t)255);
+  auto take = [&](int64_t bytes) {
+    char* at = p;
+    p += al256(bytes);
+    return at;
+  };
   SplitWs ws;
-  ws.st = (RowState*)p;
-  p += al((int64_t)B * sizeof(RowState));
-  ws.cmax = (float*)p;
-  p += al((int64_t)B * C * 4);
-  ws.hist = (uint64_t*)p;
-  p += al((int64_t)B * C * kMaxBins * 8);
-  ws.ties = (uint64_t*)p;
-  const dim3 grid(C, B);
-  split_chunk_max<<<grid, kST, 0, stream>>>(V, C, logits, ws);
-  for (int r = 0; r < kRounds; ++r) {
-    split_chunk_hist<<<grid, kST, 0, stream>>>(V, C, r, logits, inv_t, ws);
-    split_select<<<B, kThreads, 0, stream>>>(C, r, p24, ws);
-  }
-  split_chunk_ties<<<grid, kST, 0, stream>>>(V, C, logits, inv_t, ws);
-  split_walk<<<B, kST, 0, stream>>>(V, C, logits, inv_t, uniforms, tokens, ws);
+  ws.C = C;
+  ws.cap = sample_list_cap(C);
+  ws.st = (RowState*)take((int64_t)B * sizeof(RowState));
+  ws.cmax = (float*)take((int64_t)B * C * 4);
+  ws.hist = (uint64_t*)take((int64_t)B * C * kBins * 8);
+  ws.bmass = (uint64_t*)take((int64_t)B * kMaxBlocks * 8);
+  ws.count = (int*)take((int64_t)B * C * 4);
+  ws.list_z = (float*)take((int64_t)B * C * ws.cap * 4);
+  ws.list_i = (int*)take((int64_t)B * C * ws.cap * 4);
+  if (vec)
+    launch_split<true>(B, V, logits, inv_t, p24, uniforms, tokens, ws, stream);
+  else
+    launch_split<false>(B, V, logits, inv_t, p24, uniforms, tokens, ws, stream);
   return hipGetLastError();
 }
 
