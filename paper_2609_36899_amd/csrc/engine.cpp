@@ -480,6 +480,8 @@ int enqueue_forward(pdec_engine* E, const Pass& p, const int32_t* tokens_dev, fl
   hipStream_t s = E->stream;
   const int n_items = (int)p.items.size(), n_qb = (int)p.qblocks.size();
   const int max_items = max_items_per_qblock(p.qblocks);
+  // fp32: with one item per block the split pass writes the output itself.
+  const bool direct = dt == PDEC_F32 && max_items == 1;
 
   HIP_OR_FAIL(launch_embed_norm(dt, M, d, c.vocab, d_tok, E->embed, E->attn_norm[0], c.rms_eps, E->x,
                                 E->h, s));
@@ -500,15 +502,18 @@ int enqueue_forward(pdec_engine* E, const Pass& p, const int32_t* tokens_dev, fl
                                        n_items, c.n_q_heads, c.n_kv_heads,
                                        d_it, d_qb,
                                        E->q, E->k_layer(l), E->v_layer(l), E->page_stride, E->bt,
-                                       E->ws.bt_stride, E->att_ml, E->att_acc, s, ea, eb));
-    if (rows_per_item == kDecodeRows)
-      HIP_OR_FAIL(launch_attention_combine(Dh, rows_per_item, n_qb, max_items, c.n_q_heads,
-                                           c.n_kv_heads, d_qb, E->att_ml, E->att_acc, E->o,
-                                           dt == PDEC_BF16, s));
-    else  // prefill: up to 128 rows and few items per block
-      HIP_OR_FAIL(launch_attention_combine_rows(Dh, rows_per_item, n_qb, c.n_q_heads,
-                                                c.n_kv_heads, d_qb, E->att_ml, E->att_acc, E->o,
-                                                dt == PDEC_BF16, s));
+                                       E->ws.bt_stride, E->att_ml, E->att_acc, s, ea, eb,
+                                       direct ? (float*)E->o : nullptr));
+    if (!direct) {
+      if (rows_per_item == kDecodeRows)
+        HIP_OR_FAIL(launch_attention_combine(Dh, rows_per_item, n_qb, max_items, c.n_q_heads,
+                                             c.n_kv_heads, d_qb, E->att_ml, E->att_acc, E->o,
+                                             dt == PDEC_BF16, s));
+      else  // prefill: up to 128 rows and few items per block
+        HIP_OR_FAIL(launch_attention_combine_rows(Dh, rows_per_item, n_qb, c.n_q_heads,
+                                                  c.n_kv_heads, d_qb, E->att_ml, E->att_acc, E->o,
+                                                  dt == PDEC_BF16, s));
+    }
     S = gemm_plan_splits(dt, M, d, qd, &ks);
     HIP_OR_FAIL(E->timer.pair(PDEC_TIMER_GEMM, &ea, &eb));
     HIP_OR_FAIL(launch_gemm(dt, M, d, qd, E->o, qd, E->w_o[l], E->part, S, ks, s, ea, eb));
@@ -519,8 +524,15 @@ int enqueue_forward(pdec_engine* E, const Pass& p, const int32_t* tokens_dev, fl
       HIP_OR_FAIL(launch_gemm_swiglu(M, F, d, E->h, d, E->w_gu[l].ptr[0], E->w_gu[l].ptr[1],
                                      E->u, E->part, s, ea, eb));
     } else {
-      HIP_OR_FAIL(launch_gemm(dt, M, 2 * F, d, E->h, d, E->w_gu[l], E->part, S, ks, s, ea, eb));
-      HIP_OR_FAIL(launch_swiglu(dt, M, F, E->part, S, E->u, s));
+      hipError_t fe = hipSuccess;
+      if (dt == PDEC_F32 && S == 1 &&
+          launch_gemm_f32_swiglu(M, F, d, (const float*)E->h, (const float*)E->w_gu[l].ptr[0],
+                                 (const float*)E->w_gu[l].ptr[1], (float*)E->u, s, &fe, ea, eb)) {
+        HIP_OR_FAIL(fe);
+      } else {
+        HIP_OR_FAIL(launch_gemm(dt, M, 2 * F, d, E->h, d, E->w_gu[l], E->part, S, ks, s, ea, eb));
+        HIP_OR_FAIL(launch_swiglu(dt, M, F, E->part, S, E->u, s));
+      }
     }
     S = gemm_plan_splits(dt, M, d, F, &ks);
     HIP_OR_FAIL(E->timer.pair(PDEC_TIMER_GEMM, &ea, &eb));
@@ -1181,6 +1193,13 @@ int swiglu_projection(int32_t dtype, int32_t M, int32_t F, int32_t K, const void
                                    need > 0 ? (float*)workspace : nullptr, s));
     return PDEC_OK;
   }
+  hipError_t fe = hipSuccess;
+  if (dtype == PDEC_F32 && S == 1 &&
+      launch_gemm_f32_swiglu(M, F, K, (const float*)x, (const float*)w_gate, (const float*)w_up,
+                             (float*)u, s, &fe)) {
+    HIP_OR_FAIL(fe);
+    return PDEC_OK;
+  }
   WSegs ws{};
   ws.ptr[0] = w_gate;
   ws.ptr[1] = w_up;
@@ -1253,16 +1272,20 @@ static int paged_attention_impl(int32_t kv_dtype, float k_scale, float v_scale, 
     HIP_OR_FAIL(g_attn_staging->upload(base, hm.data(), o_ml, s));
   }
   const int64_t page_stride = (int64_t)Hkv * kPage * Dh;
+  const int max_items = max_items_per_qblock(qblocks);
+  const bool direct = kv_dtype == PDEC_F32 && max_items == 1;
   HIP_OR_FAIL(launch_attention_split(kv_dtype == PDEC_F32 ? PDEC_F32 : PDEC_BF16,
                                      kv_dtype == PDEC_FP8_E4M3, k_scale, v_scale, Dh, kDecodeRows,
                                      (int)items.size(), Hq, Hkv,
                                      (const AttnItem*)(base + o_it),
                                      (const AttnQBlock*)(base + o_qb), q, k_pages, v_pages,
                                      page_stride, bt, bt_stride, (float*)(base + o_ml),
-                                     (float*)(base + o_acc), s));
-  HIP_OR_FAIL(launch_attention_combine(Dh, kDecodeRows, B, max_items_per_qblock(qblocks), Hq,
-                                       Hkv, (const AttnQBlock*)(base + o_qb),
-                                       (float*)(base + o_ml), (float*)(base + o_acc), out, 0, s));
+                                     (float*)(base + o_acc), s, nullptr, nullptr,
+                                     direct ? out : nullptr));
+  if (!direct)
+    HIP_OR_FAIL(launch_attention_combine(Dh, kDecodeRows, B, max_items, Hq, Hkv,
+                                         (const AttnQBlock*)(base + o_qb), (float*)(base + o_ml),
+                                         (float*)(base + o_acc), out, 0, s));
   return PDEC_OK;
 }
 

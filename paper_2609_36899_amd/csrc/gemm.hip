@@ -599,6 +599,74 @@ __global__ __launch_bounds__(256) void gemm_f32_tiled(int M, int N, int K, int k
     }
 }
 
+// fp32, up to 16 rows: a wave owns NC columns and every row (MP >= M), its lanes
+// take K in steps of 256 (16 bytes of each weight row and activation row), and
+// the NC * MP lane sums are reduced together: each of the first log2(NC * MP)
+// exchange steps halves the number of values a lane carries, so 16 values cost
+// 17 exchanges instead of 96, and lane i ends with one finished value.  One wave
+// per work group and no K split: these products are latency (the tiled kernel's
+// loop of loads, barriers and 16-deep products took 11.6 us on average for the
+// small decoder's projections, 4 rows, plus the split sums in its consumers;
+// this takes 5.7).  GLU: NC columns of the gate matrix and of the up matrix,
+// gate in the lower half of the values, so the halves of the wave end with g and
+// up of the same outputs and one more exchange gives silu(g) * up.
+template <int NC, int MP, bool GLU>
+__global__ __launch_bounds__(64) void gemm_f32_rows(int M, int N, int K,
+                                                    const float* __restrict__ A, int64_t lda,
+                                                    WSegs w, float* __restrict__ out) {
+  constexpr int NW = GLU ? 2 * NC : NC, V = NW * MP;
+  const int lane = threadIdx.x, n0 = blockIdx.x * NC;
+  const float* wr[NW];
+#pragma unroll
+  for (int c = 0; c < NW; ++c) {
+    const int n = min(n0 + c % NC, N - 1);  // columns past N are computed, not written
+    wr[c] = GLU ? (const float*)w.ptr[c / NC] + (int64_t)n * K
+                : (const float*)seg_row(w, n, K, 4);
+  }
+  float v[V];
+#pragma unroll
+  for (int i = 0; i < V; ++i) v[i] = 0.f;
+#pragma unroll 2
+  for (int k = lane * 4; k < K; k += 256) {  // K % 4 == 0
+    float4 a[MP], b[NW];
+#pragma unroll
+    for (int c = 0; c < NW; ++c) b[c] = *(const float4*)(wr[c] + k);
+#pragma unroll
+    for (int m = 0; m < MP; ++m) a[m] = *(const float4*)(A + (int64_t)min(m, M - 1) * lda + k);
+#pragma unroll
+    for (int c = 0; c < NW; ++c)
+#pragma unroll
+      for (int m = 0; m < MP; ++m) {
+        float s = v[c * MP + m];
+        s = fmaf(a[m].x, b[c].x, s);
+        s = fmaf(a[m].y, b[c].y, s);
+        s = fmaf(a[m].z, b[c].z, s);
+        v[c * MP + m] = fmaf(a[m].w, b[c].w, s);
+      }
+  }
+  int bit = 32;
+#pragma unroll
+  for (int half = V / 2; half > 0; half /= 2) {  // lanes with `bit` keep the upper half
+    const bool up = lane & bit;
+#pragma unroll
+    for (int i = 0; i < half; ++i) {
+      const float send = up ? v[i] : v[i + half], keep = up ? v[i + half] : v[i];
+      v[i] = keep + __shfl_xor(send, bit, 64);
+    }
+    bit /= 2;
+  }
+  float r = v[0];
+#pragma unroll
+  for (int b = 32 / V; b > 0; b /= 2) r += __shfl_xor(r, b, 64);
+  const int idx = lane / (64 / V);  // this lane's value: column idx / MP, row idx % MP
+  if constexpr (GLU) {
+    const float u = __shfl_xor(r, 32, 64);
+    r = r / (1.f + expf(-r)) * u;  // in the lower half of the wave
+  }
+  const int c = idx / MP, m = idx % MP, n = n0 + c;
+  if (lane % (64 / V) == 0 && c < NC && n < N && m < M) out[(int64_t)m * N + n] = r;
+}
+
 }  // namespace
 
 // Kernel choice for bf16, from measurements on the 8B projection shapes:
@@ -619,6 +687,13 @@ int tile_rows(int M) { return M <= 128 ? 128 : 256; }
 bool wide_tiles(int M, int64_t groups) {
   return M > 256 && ((groups + 1) / 2) * ((M + 255) / 256) >= 224;
 }
+
+// The fp32 kernel for few rows reads 16 bytes of weight and activation rows at
+// a time; above 16 rows its per-wave weight reads would be repeated by more
+// waves than the tiled kernel's.
+constexpr int kF32RowsMax = 16;
+static bool f32_rows_shape(int M, int K) { return M <= kF32RowsMax && K % 4 == 0; }
+static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 int gemm_plan_splits(int dtype, int M, int N, int K, int* k_split) {
   const int kq = (dtype == 1) ? 64 : 16;
@@ -651,7 +726,9 @@ int gemm_plan_splits(int dtype, int M, int N, int K, int* k_split) {
     }
   } else {
     const int64_t groups = (int64_t)((N + 63) / 64) * ((M + 31) / 32);
-    if (groups < 512) s = (int)std::min<int64_t>((512 + groups - 1) / groups, 8);
+    if (f32_rows_shape(M, K))
+      s = 1;  // gemm_f32_rows
+    else if (groups < 512) s = (int)std::min<int64_t>((512 + groups - 1) / groups, 8);
   }
   s = std::max(1, std::min(s, ksteps));
   const int steps_per = (ksteps + s - 1) / s;
@@ -779,6 +856,42 @@ hipError_t launch_gemm_swiglu(int M, int F, int K, const void* A, int64_t lda, c
   return e;
 }
 
+namespace {
+
+// 16 lane values per wave (8 columns of one row, 4 of up to four rows, ...).
+template <bool GLU>
+hipError_t launch_f32_rows(int M, int N, int K, const float* A, int64_t lda, const WSegs& w,
+                           float* out, hipStream_t stream, hipEvent_t ev_start,
+                           hipEvent_t ev_stop) {
+#define PDEC_F32_ROWS(NC_, MP_)                                                                \
+  return launch_timed(gemm_f32_rows<NC_, MP_, GLU>, dim3((N + NC_ - 1) / NC_), dim3(64), stream, \
+                      ev_start, ev_stop, M, N, K, A, lda, w, out)
+  if (M == 1) PDEC_F32_ROWS(4, 1);
+  if (M == 2) PDEC_F32_ROWS(4, 2);
+  if (M <= 4) PDEC_F32_ROWS((GLU ? 2 : 4), 4);
+  if (M <= 8) PDEC_F32_ROWS(2, 8);
+  PDEC_F32_ROWS(1, 16);
+#undef PDEC_F32_ROWS
+}
+
+}  // namespace
+
+bool launch_gemm_f32_swiglu(int M, int F, int K, const float* A, const float* w_gate,
+                            const float* w_up, float* u, hipStream_t stream, hipError_t* err,
+                            hipEvent_t ev_start, hipEvent_t ev_stop) {
+  *err = hipSuccess;
+  if (!f32_rows_shape(M, K) || !aligned16(A) || !aligned16(w_gate) || !aligned16(w_up))
+    return false;
+  WSegs w{};
+  w.ptr[0] = w_gate;
+  w.ptr[1] = w_up;
+  w.row_end[0] = F;
+  w.row_end[1] = 2 * F;
+  w.n_seg = 2;
+  *err = launch_f32_rows<true>(M, F, K, A, K, w, u, stream, ev_start, ev_stop);
+  return true;
+}
+
 hipError_t launch_gemm(int dtype, int M, int N, int K, const void* A, int64_t lda,
                        const WSegs& w_in, float* out, int splits, int k_split, hipStream_t stream,
                        hipEvent_t ev_start, hipEvent_t ev_stop) {
@@ -796,6 +909,11 @@ hipError_t launch_gemm(int dtype, int M, int N, int K, const void* A, int64_t ld
     return launch_gemm_bf16<false>(M, N, K, (const uint16_t*)A, lda, w, n_groups, out, nullptr,
                                    splits, k_split, stream, ev_start, ev_stop);
   } else {
+    if (splits == 1 && f32_rows_shape(M, K) && lda % 4 == 0 && aligned16(A) &&
+        aligned16(w_in.ptr[0]) && (w_in.n_seg < 2 || aligned16(w_in.ptr[1])) &&
+        (w_in.n_seg < 3 || aligned16(w_in.ptr[2])))
+      return launch_f32_rows<false>(M, N, K, (const float*)A, lda, w_in, out, stream, ev_start,
+                                    ev_stop);
     const dim3 grid((N + 63) / 64, (M + 31) / 32, splits);
     return launch_timed(gemm_f32_tiled, grid, block, stream, ev_start, ev_stop, M, N, K, k_split,
                         (const float*)A, lda, w_in, out);

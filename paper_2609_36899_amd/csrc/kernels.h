@@ -29,6 +29,9 @@ struct WSegs {
 // statistics part_ml [items][Hkv][rows_per_item][2] = (max in log2 units,
 // sum) and unnormalised outputs part_acc [items][Hkv][rows_per_item][head_dim].
 // kv_fp8: K/V pages hold E4M3 codes read back as code * k_scale / v_scale.
+// f32_out (fp32 path, only when every query block has a single item): the pass
+// writes the normalised rows [rows][n_q_heads][head_dim] there instead of
+// partials, and no merge pass is needed.
 hipError_t launch_attention_split(int dtype, int kv_fp8, float k_scale, float v_scale,
                                   int head_dim, int rows_per_item, int n_items,
                                   int n_q_heads,
@@ -37,7 +40,8 @@ hipError_t launch_attention_split(int dtype, int kv_fp8, float k_scale, float v_
                                   const void* v_pages, int64_t page_stride_elems,
                                   const int32_t* block_table, int32_t bt_stride, float* part_ml,
                                   float* part_acc, hipStream_t stream,
-                                  hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+                                  hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr,
+                                  float* f32_out = nullptr);
 
 // The LDS-staged prefill kernel (attention_prefill.hip) behind
 // launch_attention_split for 128- or 256-row items with 128-dim heads, bf16
@@ -89,6 +93,12 @@ hipError_t launch_gemm(int dtype, int M, int N, int K, const void* A, int64_t ld
 hipError_t launch_gemm_swiglu(int M, int F, int K, const void* A, int64_t lda, const void* w_gate,
                               const void* w_up, void* u, float* tail_part, hipStream_t stream,
                               hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+// fp32 gate/up projection with SwiGLU for up to kF32RowsMax rows in one kernel
+// (u[m][n] as launch_gemm over the two segments and launch_swiglu give it);
+// false where the shape or an alignment rules it out and nothing was enqueued.
+bool launch_gemm_f32_swiglu(int M, int F, int K, const float* A, const float* w_gate,
+                            const float* w_up, float* u, hipStream_t stream, hipError_t* err,
+                            hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 // fp32 elements launch_gemm_swiglu needs in tail_part for this shape (0: fused only).
 int64_t swiglu_tail_part_elems(int M, int F, int K);
 // Temperature / top-p sampling (sample.hip).

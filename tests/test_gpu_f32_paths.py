@@ -1,0 +1,79 @@
+"""The fp32 kernels at the edges of their tiles, against float64.
+
+Attention: context lengths around the 16-token pages, the 64-key tiles and the
+128-key items (one item: normalised in the split pass; several: merged), GQA
+groups that fill a wave's rows unevenly, slots past a context's end NaN.
+Projections: row counts around each form of the few-row kernel and its limit of
+16, K around its 256-wide steps, columns that do not fill a wave, and inputs
+that are not 16-byte aligned (the tiled kernel).
+
+Tolerances: a lane adds at most K/64 + 16 products (attention: dims, then keys)
+in a chain of fp32 roundings, so |error| <= (n + 16) 2^-24 sum |a||b| for a
+projection; attention outputs are convex sums of N(0, 1) values whose weights
+carry the score's error, (dims + keys/64 + 16) 2^-24 times scores of size < 16.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _attention64(q, k, v):
+    """q [Hq][Dh], k and v [n][Hkv][Dh] in float64."""
+    hq, dh = q.shape
+    g = hq // k.shape[1]
+    out = np.empty_like(q)
+    for h in range(hq):
+        s = k[:, h // g] @ q[h] / np.sqrt(dh)
+        p = np.exp(s - s.max())
+        out[h] = (p / p.sum()) @ v[:, h // g]
+    return out
+
+
+@pytest.mark.parametrize("hq,hkv,dh", [(4, 2, 64), (5, 1, 128), (16, 1, 64), (12, 4, 128), (2, 2, 64)])
+@pytest.mark.parametrize("lens", [(1, 15, 16, 17), (63, 64, 65, 127), (128,), (129, 3, 1000, 640)])
+def test_attention_tile_edges(hq, hkv, dh, lens):
+    import paper_2609_36899_amd as P
+    from workload import paged_attention_case
+    case = paged_attention_case(len(lens), hq, hkv, dh, np.array(lens), 200, seed=7 + dh, bf16=False)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    out = torch.full((len(lens), hq, dh), np.nan, device="cuda")
+    bt = dev(np.maximum(case.block_table, 0))
+    P.paged_decode_attention(dev(case.q), dev(case.k_pool), dev(case.v_pool.transpose(0, 1, 3, 2)),
+                             bt, lens, out)
+    got = out.cpu().numpy()
+    for b, n in enumerate(lens):
+        pages = case.block_table[b, :(n + 15) // 16]
+        flat = lambda pool: pool[pages].transpose(0, 2, 1, 3).reshape(-1, hkv, dh)[:n].astype(np.float64)
+        ref = _attention64(case.q[b].astype(np.float64), flat(case.k_pool), flat(case.v_pool))
+        tol = (dh + n / 64 + 16) * 2.0 ** -24 * 16
+        assert np.max(np.abs(got[b] - ref)) <= tol
+
+
+@pytest.mark.parametrize("M", [1, 2, 3, 4, 5, 8, 9, 16, 17])
+@pytest.mark.parametrize("N,K,shift", [(4, 4, 0), (516, 252, 0), (1024, 256, 0), (260, 688, 0),
+                                       (64, 1030, 0), (132, 256, 1)])
+def test_projection_rows(M, N, K, shift):
+    import paper_2609_36899_amd as P
+    rng = np.random.default_rng(M * 1000 + K)
+    x, w, w2 = (rng.standard_normal(s).astype(np.float32) for s in ((M, K), (N, K), (N, K)))
+    buf = torch.empty(shift + M * K, device="cuda")
+    xd = buf[shift:].view(M, K)
+    xd.copy_(torch.from_numpy(x))
+    wd, wd2 = (P.pack_weight(torch.from_numpy(a).cuda()) for a in (w, w2))
+    x64, w64, u64 = x.astype(np.float64), w.astype(np.float64), w2.astype(np.float64)
+    eps = (K / 64 + 16) * 2.0 ** -24
+    out = torch.full((M, N), np.nan, device="cuda")
+    P.weight_projection(xd, wd, out)
+    bound = eps * (np.abs(x64) @ np.abs(w64).T)
+    assert np.all(np.abs(out.cpu().numpy() - x64 @ w64.T) <= bound)
+    u = torch.full((M, N), np.nan, device="cuda")
+    P.swiglu_projection(xd, wd, wd2, u)
+    g, up = x64 @ w64.T, x64 @ u64.T
+    ref = g / (1 + np.exp(-g)) * up
+    # d silu <= 1.1 per unit of g; expf and the divide add a few roundings.
+    tol = 1.1 * bound * np.abs(up) + eps * (np.abs(x64) @ np.abs(u64).T) * np.abs(g) + \
+        8 * 2.0 ** -24 * np.abs(ref) + 1e-30
+    assert np.all(np.abs(u.cpu().numpy() - ref) <= tol)
