@@ -266,10 +266,10 @@ size_t part_elems_for(const pdec_model_cfg* c, int64_t rows_cap) {
                             {c->d_model, c->ffn_dim}};
   size_t best = 0;
   for (int64_t m = 1; m <= rows_cap; ++m) {
-    for (auto& s : shapes) {
+    for (int i = 0; i < 4; ++i) {
       int ks;
-      const int S = gemm_plan_splits(c->dtype, (int)m, s[0], s[1], &ks);
-      best = std::max(best, (size_t)S * (size_t)m * (size_t)s[0]);
+      const int S = gemm_plan_splits(c->dtype, (int)m, shapes[i][0], shapes[i][1], &ks, i == 2);
+      best = std::max(best, (size_t)S * (size_t)m * (size_t)shapes[i][0]);
     }
     if (c->dtype == PDEC_BF16)  // the split tail of a fused gate/up launch
       best = std::max(best, (size_t)swiglu_tail_part_elems((int)m, c->ffn_dim, c->d_model));
@@ -518,7 +518,7 @@ int enqueue_forward(pdec_engine* E, const Pass& p, const int32_t* tokens_dev, fl
     HIP_OR_FAIL(E->timer.pair(PDEC_TIMER_GEMM, &ea, &eb));
     HIP_OR_FAIL(launch_gemm(dt, M, d, qd, E->o, qd, E->w_o[l], E->part, S, ks, s, ea, eb));
     HIP_OR_FAIL(launch_resid_norm(dt, M, d, E->part, S, E->x, E->ffn_norm[l], c.rms_eps, E->h, s));
-    S = gemm_plan_splits(dt, M, 2 * F, d, &ks);
+    S = gemm_plan_splits(dt, M, 2 * F, d, &ks, true);
     HIP_OR_FAIL(E->timer.pair(PDEC_TIMER_GEMM, &ea, &eb));
     if (dt == PDEC_BF16 && S == 1) {  // one work group per column: SwiGLU in the epilogue
       HIP_OR_FAIL(launch_gemm_swiglu(M, F, d, E->h, d, E->w_gu[l].ptr[0], E->w_gu[l].ptr[1],
@@ -1168,7 +1168,7 @@ int64_t swiglu_projection_workspace_bytes(int32_t dtype, int32_t M, int32_t F, i
   if ((dtype != PDEC_F32 && dtype != PDEC_BF16) || M < 1 || F < 1 || K < 1 || F > INT32_MAX / 2)
     return fail(PDEC_INVALID_ARG, "bad projection arguments");
   int ks;
-  const int S = gemm_plan_splits(dtype, M, 2 * F, K, &ks);
+  const int S = gemm_plan_splits(dtype, M, 2 * F, K, &ks, true);
   return (dtype == PDEC_BF16 && S == 1) ? swiglu_tail_part_elems(M, F, K) * 4
                                          : (int64_t)S * M * 2 * F * 4;
 }
@@ -1185,7 +1185,7 @@ int swiglu_projection(int32_t dtype, int32_t M, int32_t F, int32_t K, const void
   if (ws_bytes < need || (need > 0 && !workspace))
     return fail(PDEC_INVALID_ARG, "workspace too small: need " + std::to_string(need));
   int ks;
-  const int S = gemm_plan_splits(dtype, M, 2 * F, K, &ks);
+  const int S = gemm_plan_splits(dtype, M, 2 * F, K, &ks, true);
   hipStream_t s = (hipStream_t)stream;
   // The same choice as the decoder layer.
   if (dtype == PDEC_BF16 && S == 1) {

@@ -186,6 +186,67 @@ __global__ __launch_bounds__(256) void gemm_bf16_stream(int M, int N, int K, int
   }
 }
 
+// Few rows and few columns (at most 16 rows and 256 strips; o and, up to nine
+// rows, down of the 8B shape): one work group per 16-column strip, its eight
+// waves taking an eighth of K each and adding up through LDS in wave order.  The
+// strips alone fill the GPU, so nothing is split over the grid: no partial sums
+// in memory, no pass that adds them, one slab for the consumer.  A wave keeps
+// eight k-blocks of 32 (1 KiB of weights and as much of activations each) in
+// flight, with K = 4096 half of its share; 16 in flight was no faster, nor was
+// placing a group's strips on one XCD.  Each work group reads all of A, at 16
+// rows as many bytes as its weights, which is what ends the form (see
+// strip_form).  o (4096 x 4096), us per weight_projection, streaming kernel and
+// split sum against this: 9.9 / 7.8 at 1 row, 10.6 / 9.2 at 16.
+constexpr int kStripWaves = 8;
+__global__ __launch_bounds__(64 * kStripWaves) void gemm_bf16_strip(
+    int M, int N, int K, const uint16_t* __restrict__ A, int64_t lda, WSegs w,
+    float* __restrict__ out) {
+  constexpr int NS = 8;
+  __shared__ __attribute__((aligned(16))) f32x4 red[kStripWaves][64];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int c16 = lane & 15, q4 = lane >> 4;
+  const int strip = blockIdx.x & 7;
+  const GroupRef gr = group_ref(w, blockIdx.x >> 3, K);
+  const int kb_all = K / 32, per = (kb_all + kStripWaves - 1) / kStripWaves;
+  const int kb0 = min(wave * per, kb_all), n = min(per, kb_all - kb0);  // this wave's k-blocks
+  const uint16_t* wp = gr.base + ((int64_t)kb0 * 8 + strip) * 512 + lane * 8;
+  const uint16_t* ap = A + (int64_t)min(c16, M - 1) * lda + kb0 * 32 + q4 * 8;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  if (n > 0) {
+    bf16x8 rw[NS], ra[NS];
+    // As in the streaming kernel: branch-free refills (clamped to the last
+    // block) pinned behind the slot's use keep all NS slots in flight.
+    const int last = n - 1;
+    auto load = [&](int i, bf16x8& wr, bf16x8& ar) {
+      wr = load_stream<bf16x8>(wp + (int64_t)i * 4096);
+      ar = *(const bf16x8*)(ap + i * 32);
+    };
+#pragma unroll
+    for (int s = 0; s < NS; ++s) load(min(s, last), rw[s], ra[s]);
+    int it = 0;
+    for (; it + NS < n; it += NS) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ra[s], rw[s], acc, 0, 0, 0);
+        load(min(it + s + NS, last), rw[s], ra[s]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+      if (s < n - it) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ra[s], rw[s], acc, 0, 0, 0);
+  }
+  red[wave][lane] = acc;
+  __syncthreads();
+  if (wave > 0) return;
+#pragma unroll
+  for (int v = 1; v < kStripWaves; ++v) acc += red[v][lane];
+  const int col = gr.col0 + strip * 16 + c16;
+#pragma unroll
+  for (int rr = 0; rr < 4; ++rr)
+    if (4 * q4 + rr < M && col < gr.col_end) out[(int64_t)(4 * q4 + rr) * N + col] = acc[rr];
+}
+
 // Larger batches (M > 32): (64 WM) x 128 output tiles, 2 WM waves in a WM x 2
 // grid of 64 x 64 sub-tiles.  Per k-step of 64 the A tile and the W tile are
 // staged once through LDS and each is shared by the waves that need it.  The
@@ -670,7 +731,8 @@ __global__ __launch_bounds__(64) void gemm_f32_rows(int M, int N, int K,
 }  // namespace
 
 // Kernel choice for bf16, from measurements on the 8B projection shapes:
-//  * M <= 32: the streaming kernel (two strips per wave, ring depth 2);
+//  * M <= 32: the streaming kernel (two strips per wave, ring depth 2), or the
+//    strip kernel (strip_form);
 //    6.0-6.6 TB/s of weights up to M = 16;
 //  * larger M: the 128 x 128 tile (M <= 128) or 256 x 128 tile, and above
 //    256 rows the 256 x 256 tile where its grid fills the GPU.
@@ -688,6 +750,15 @@ bool wide_tiles(int M, int64_t groups) {
   return M > 256 && ((groups + 1) / 2) * ((M + 255) / 256) >= 224;
 }
 
+// Where the strip kernel takes a projection: its strips fit the 256 CUs once
+// (320 strips, 5120 columns, left a quarter of the CUs two: 13.5 us against 12.1
+// at one row) and the activations every work group reads, M * K * 2 bytes, stay
+// under 256 KiB (down of the 8B shape, K 14336, us against the streaming kernel
+// and its split sum: 20.2 / 22.2 at 1 row, 21.7 / 22.8 at 8, 24.4 / 23.1 at 12).
+static bool strip_form(int M, int K, int64_t groups) {
+  return M <= 16 && groups <= 32 && (int64_t)M * K <= 131072;
+}
+
 // The fp32 kernel for few rows reads 16 bytes of weight and activation rows at
 // a time; above 16 rows its per-wave weight reads would be repeated by more
 // waves than the tiled kernel's.
@@ -695,13 +766,17 @@ constexpr int kF32RowsMax = 16;
 static bool f32_rows_shape(int M, int K) { return M <= kF32RowsMax && K % 4 == 0; }
 static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
-int gemm_plan_splits(int dtype, int M, int N, int K, int* k_split) {
+int gemm_plan_splits(int dtype, int M, int N, int K, int* k_split, bool glu) {
   const int kq = (dtype == 1) ? 64 : 16;
   const int ksteps = (K + kq - 1) / kq;
   int s = 1;
   if (dtype == 1) {
     // Work groups per split: one per 128-column group (times the M-blocks).
     int64_t groups = (N + kGroupCols - 1) / kGroupCols;
+    if (!glu && strip_form(M, K, groups)) {  // K is split inside its work groups
+      *k_split = K;
+      return 1;
+    }
     if (wide_tiles(M, groups)) groups = ((groups + 1) / 2) * ((M + 255) / 256);
     else if (M > kStreamMaxRows) groups *= (M + tile_rows(M) - 1) / tile_rows(M);
     // Measured on the 8B shapes with weights streamed from HBM: the best
@@ -756,6 +831,11 @@ hipError_t launch_gemm_bf16(int M, int N, int K, const uint16_t* a, int64_t lda,
                             hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
   // Plain matrices given as several segments (q|k|v) keep the 256 x 128 tile.
   const bool wide = wide_tiles(M, n_groups) && (GLU || w.n_seg == 1);
+  if constexpr (!GLU) {
+    if (splits == 1 && strip_form(M, K, n_groups))
+      return launch_timed(gemm_bf16_strip, dim3(n_groups * 8), dim3(64 * kStripWaves), stream,
+                          ev_start, ev_stop, M, N, K, a, lda, w, out);
+  }
   if (M <= kStreamMaxRows) {
     const dim3 grid(n_groups, 1, splits);
     if (M <= 16)

@@ -118,7 +118,9 @@ hipError_t launch_sample_top_p(int B, int V, const float* logits, float temperat
 hipError_t launch_pack_weight(int dtype, int N, int K, const void* w, void* packed,
                               hipStream_t stream);
 // Number of K splits the launcher plans for this shape (and the split size).
-int gemm_plan_splits(int dtype, int M, int N, int K, int* k_split);
+// glu: the gate/up product (N = 2 F), whose unsplit bf16 form is
+// launch_gemm_swiglu.
+int gemm_plan_splits(int dtype, int M, int N, int K, int* k_split, bool glu = false);
 
 // ---- per-row and elementwise steps -------------------------------------------
 // x[m] = E[tok[m]];  h[m] = rmsnorm(x[m]) * gain.  Ids are clamped to [0, vocab).

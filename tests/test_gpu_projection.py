@@ -45,6 +45,15 @@ def test_bf16_ragged_shapes(M):
     _run(M, 1412, 576, seed=M)
 
 
+@pytest.mark.parametrize("M,N,K", [
+    (1, 4096, 64), (16, 132, 64), (7, 4, 448), (16, 4096, 576), (9, 260, 1088),  # K in 8 uneven parts
+    (8, 256, 16384), (9, 256, 16384), (16, 512, 8192), (16, 512, 8256), (17, 4096, 576),  # the row limits
+    (16, 4096, 4096), (4, 4100, 256)])  # 256 strips and one more group
+def test_bf16_strip_form_limits(M, N, K):
+    """The one-strip-per-work-group form and its limits (rows, rows x K, columns)."""
+    _run(M, N, K, seed=M + N + K)
+
+
 @pytest.mark.parametrize("M", [1, 3, 4, 8, 64, 256, 512])
 @pytest.mark.parametrize("N,K", [(6144, 4096), (4096, 14336)])
 def test_bf16_8b_shapes_sampled_rows(M, N, K):
