@@ -33,24 +33,94 @@ __device__ __forceinline__ float4 add_splits4(float4 v, const float* p, int64_t 
   return v;
 }
 
-__device__ __forceinline__ float add_splits1(float v, const float* p, int64_t slab, int n) {
-  for (int s0 = 0; s0 < n; s0 += 8) {
-    float t[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (s0 + u < n) t[u] = p[(int64_t)(s0 + u) * slab];
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (s0 + u < n) v += t[u];
+template <typename HT>
+struct Pack4;
+template <>
+struct Pack4<float> {
+  static __device__ __forceinline__ void store(float* p, float4 v) { *(float4*)p = v; }
+};
+template <>
+struct Pack4<uint16_t> {
+  static __device__ __forceinline__ void store(uint16_t* p, float4 v) {
+    const uint32_t lo = (uint32_t)f32_to_bf16(v.x) | ((uint32_t)f32_to_bf16(v.y) << 16);
+    const uint32_t hi = (uint32_t)f32_to_bf16(v.z) | ((uint32_t)f32_to_bf16(v.w) << 16);
+    *(uint2*)p = make_uint2(lo, hi);
   }
-  return v;
-}
+};
 
 // Token ids from the caller's device buffer cannot be checked on the host
 // without a synchronisation; out-of-range ids are clamped so that they read
 // a valid embedding row instead of faulting.
+// One work group of up to 1024 threads per row, four elements per access, the
+// row kept in registers between the two passes and the gains loaded before the
+// reduction: the launch is a chain of latencies (token id, table row, sum), so
+// element-wise loads and a second read of x cost 11 us at 16 rows and 52 us at
+// 4096, against 4.4 and 34.
+template <typename T>
+__device__ __forceinline__ float4 load4(const T* p);
+template <>
+__device__ __forceinline__ float4 load4<float>(const float* p) { return *(const float4*)p; }
+template <>
+__device__ __forceinline__ float4 load4<uint16_t>(const uint16_t* p) {
+  const uint2 v = *(const uint2*)p;
+  return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u),
+                     __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xFFFF0000u));
+}
+
+constexpr int kRowKeep = 4;  // float4s per thread kept in registers between a row's passes
+
 template <typename WT, typename HT>
-__global__ __launch_bounds__(kRowThreads) void embed_norm_kernel(
+__global__ __launch_bounds__(1024) void embed_norm_kernel(
+    int d, int vocab, const int32_t* __restrict__ tokens, const WT* __restrict__ embed,
+    const float* __restrict__ gain, float eps, float* __restrict__ x, HT* __restrict__ h) {
+  __shared__ float red[16];
+  const int row = blockIdx.x;
+  const int tok = min(max(tokens[row], 0), vocab - 1);
+  const WT* e = embed + (int64_t)tok * d;
+  float* xr = x + (int64_t)row * d;
+  const int stride = blockDim.x * 4;
+  float4 keep[kRowKeep], g[kRowKeep];
+  float ss = 0.f;
+#pragma unroll
+  for (int k = 0; k < kRowKeep; ++k) {
+    const int i = threadIdx.x * 4 + k * stride;
+    if (i < d) {
+      keep[k] = load4<WT>(e + i);
+      g[k] = *(const float4*)(gain + i);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < kRowKeep; ++k) {
+    const int i = threadIdx.x * 4 + k * stride;
+    if (i < d) {
+      const float4 v = keep[k];
+      *(float4*)(xr + i) = v;
+      ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+    }
+  }
+  for (int i = threadIdx.x * 4 + kRowKeep * stride; i < d; i += stride) {  // wider rows
+    const float4 v = load4<WT>(e + i);
+    *(float4*)(xr + i) = v;
+    ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+  }
+  const float inv = rsqrtf(block_sum(ss, red) / (float)d + eps);
+  HT* hr = h + (int64_t)row * d;
+  auto put = [&](int i, float4 v, float4 g4) {
+    Pack4<HT>::store(hr + i, make_float4(v.x * inv * g4.x, v.y * inv * g4.y, v.z * inv * g4.z,
+                                         v.w * inv * g4.w));
+  };
+#pragma unroll
+  for (int k = 0; k < kRowKeep; ++k) {
+    const int i = threadIdx.x * 4 + k * stride;
+    if (i < d) put(i, keep[k], g[k]);
+  }
+  for (int i = threadIdx.x * 4 + kRowKeep * stride; i < d; i += stride)
+    put(i, load4<WT>(e + i), *(const float4*)(gain + i));
+}
+
+// Rows whose width or table is not a multiple of four elements.
+template <typename WT, typename HT>
+__global__ __launch_bounds__(kRowThreads) void embed_norm_any_kernel(
     int d, int vocab, const int32_t* __restrict__ tokens, const WT* __restrict__ embed,
     const float* __restrict__ gain, float eps, float* __restrict__ x, HT* __restrict__ h) {
   __shared__ float red[kRowThreads / 64];
@@ -70,21 +140,6 @@ __global__ __launch_bounds__(kRowThreads) void embed_norm_kernel(
     hr[i] = Store<HT>::from(xr[i] * inv * gain[i]);
 }
 
-template <typename HT>
-struct Pack4;
-template <>
-struct Pack4<float> {
-  static __device__ __forceinline__ void store(float* p, float4 v) { *(float4*)p = v; }
-};
-template <>
-struct Pack4<uint16_t> {
-  static __device__ __forceinline__ void store(uint16_t* p, float4 v) {
-    const uint32_t lo = (uint32_t)f32_to_bf16(v.x) | ((uint32_t)f32_to_bf16(v.y) << 16);
-    const uint32_t hi = (uint32_t)f32_to_bf16(v.z) | ((uint32_t)f32_to_bf16(v.w) << 16);
-    *(uint2*)p = make_uint2(lo, hi);
-  }
-};
-
 // KV page stores: bf16 / fp32 as above; fp8 pages hold E4M3 codes of x / scale.
 template <typename T>
 struct KvStore {
@@ -103,56 +158,66 @@ struct KvStore<uint8_t> {
 };
 
 // One work group of up to 1024 threads per row, float4 accesses (d % 4 == 0).
+// The gains are loaded with the row, ahead of the reduction, not behind it.
 template <typename HT>
 __global__ __launch_bounds__(1024) void resid_norm_kernel(
     int M, int d, const float* __restrict__ part, int splits, float* __restrict__ x,
     const float* __restrict__ gain, float eps, HT* __restrict__ h) {
-  constexpr int RC = 4;  // float4s per thread kept in registers between the passes
   __shared__ float red[16];
   const int row = blockIdx.x;
   float* xr = x + (int64_t)row * d;
   const int64_t slab = (int64_t)M * d;
   const float* pr = part + (int64_t)row * d;
   const int stride = blockDim.x * 4;
-  float4 keep[RC];
+  float4 keep[kRowKeep], g[kRowKeep];
   float ss = 0.f;
 #pragma unroll
-  for (int k = 0; k < RC; ++k) {
+  for (int k = 0; k < kRowKeep; ++k) {
     const int i = threadIdx.x * 4 + k * stride;
     if (i < d) {
+      g[k] = *(const float4*)(gain + i);
       const float4 v = add_splits4(*(const float4*)(xr + i), pr + i, slab, splits);
       *(float4*)(xr + i) = v;
       keep[k] = v;
       ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
     }
   }
-  for (int i = threadIdx.x * 4 + RC * stride; i < d; i += stride) {  // rows wider than kept
+  for (int i = threadIdx.x * 4 + kRowKeep * stride; i < d; i += stride) {  // rows wider than kept
     const float4 v = add_splits4(*(const float4*)(xr + i), pr + i, slab, splits);
     *(float4*)(xr + i) = v;
     ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
   }
   const float inv = rsqrtf(block_sum(ss, red) / (float)d + eps);
   HT* hr = h + (int64_t)row * d;
-  auto put = [&](int i, float4 v) {
-    const float4 g = *(const float4*)(gain + i);
-    Pack4<HT>::store(hr + i, make_float4(v.x * inv * g.x, v.y * inv * g.y, v.z * inv * g.z,
-                                         v.w * inv * g.w));
+  auto put = [&](int i, float4 v, float4 g4) {
+    Pack4<HT>::store(hr + i, make_float4(v.x * inv * g4.x, v.y * inv * g4.y, v.z * inv * g4.z,
+                                         v.w * inv * g4.w));
   };
 #pragma unroll
-  for (int k = 0; k < RC; ++k) {
+  for (int k = 0; k < kRowKeep; ++k) {
     const int i = threadIdx.x * 4 + k * stride;
-    if (i < d) put(i, keep[k]);
+    if (i < d) put(i, keep[k], g[k]);
   }
-  for (int i = threadIdx.x * 4 + RC * stride; i < d; i += stride) put(i, *(const float4*)(xr + i));
+  for (int i = threadIdx.x * 4 + kRowKeep * stride; i < d; i += stride)
+    put(i, *(const float4*)(xr + i), *(const float4*)(gain + i));
 }
 
-// A row is handled by gridDim.y work groups.  Pairs (i, i + Dh/2) of every q and k head are
-// rotated by the table angle of the row's position, four pairs per thread;
-// v is copied.  KV pages take the element type KVT (fp8 pages store codes of
-// k / k_scale and v / v_scale).  With q/k gains (the Qwen3 family's per-head norm), each q and
-// k head is first RMS-normalised over Dh: the Dh/8 threads of a head are
-// consecutive, aligned lanes, and reduce their sum of squares by shuffles.  K goes to [page][g][slot][Dh], V to the transposed block
-// [page][g][Dh][slot].
+// Pairs (i, i + Dh/2) of every q and k head are rotated by the table angle of the
+// row's position, four pairs per thread; v is copied.  KV pages take the element
+// type KVT (fp8 pages store codes of k / k_scale and v / v_scale).  With q/k
+// gains (the Qwen3 family's per-head norm), each q and k head is first
+// RMS-normalised over Dh: the Dh/8 threads of a head are consecutive, aligned
+// lanes, and reduce their sum of squares by shuffles.  K goes to
+// [page][g][slot][Dh], V to the transposed block [page][g][Dh][slot].
+//
+// Work groups [0, M * n_parts) take a row's q and k quads (and, with v_rows = 1,
+// its v quads), one per thread; the partial sums are asked for before the row's
+// position and page, which only the stores and the table read need.  v_rows = 16
+// (many rows): work groups of their own take 16 consecutive rows of one KV head,
+// thread (dim, eight rows), so that the rows of a page, whose V elements lie side
+// by side, are written by one thread and, where they are eight slots of one page,
+// with one store; a row at a time, 4096 rows sent every 32-byte sector 16
+// two-byte writes from eight XCDs (49 us; 33 in this form).
 template <typename T, typename KVT>
 __global__ __launch_bounds__(kRowThreads) void qkv_rope_kv_kernel(
     int M, int head_dim, int n_q_heads, int n_kv_heads, const float* __restrict__ part,
@@ -160,23 +225,60 @@ __global__ __launch_bounds__(kRowThreads) void qkv_rope_kv_kernel(
     const int32_t* __restrict__ bt, int32_t bt_stride, T* __restrict__ q_out,
     KVT* __restrict__ kpool, KVT* __restrict__ vpool, int64_t page_stride,
     const float* __restrict__ q_gain, const float* __restrict__ k_gain, float eps,
-    float k_scale, float v_scale) {
-  const int row = blockIdx.x;
-  const RowMeta rm = rows[row];
+    float k_scale, float v_scale, int n_parts, int v_rows) {
   const int half = head_dim / 2;
   const int ncols = (n_q_heads + 2 * n_kv_heads) * head_dim;
+  const int vcol0 = (n_q_heads + n_kv_heads) * head_dim;
   const int64_t slab = (int64_t)M * ncols;
+  auto page_of = [&](RowMeta rm) {
+    return (int64_t)bt[(int64_t)rm.slot * bt_stride + rm.pos / kPage] * page_stride;
+  };
+  const int vb = (int)blockIdx.x - M * n_parts;
+  if (vb >= 0) {  // 16 rows x one KV head of V
+    const int r0 = vb / n_kv_heads * 16, g = vb % n_kv_heads;
+    for (int e = threadIdx.x; e < 2 * head_dim; e += kRowThreads) {
+      const int dd = e % head_dim, ra = r0 + e / head_dim * 8, n = min(8, M - ra);
+      if (n <= 0) continue;
+      const float* p = part + (int64_t)ra * ncols + vcol0 + g * head_dim + dd;
+      float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      for (int s = 0; s < splits; ++s, p += slab)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] += p[(int64_t)min(j, n - 1) * ncols];
+      const int64_t at = ((int64_t)g * head_dim + dd) * kPage;
+      const RowMeta a = rows[ra], b = rows[ra + n - 1];
+      if (n == 8 && a.slot == b.slot && b.pos - a.pos == 7 && a.pos % 8 == 0) {
+        KVT* dst = vpool + page_of(a) + at + a.pos % kPage;
+        KvStore<KVT>::store4(dst, make_float4(v[0], v[1], v[2], v[3]), v_scale);
+        KvStore<KVT>::store4(dst + 4, make_float4(v[4], v[5], v[6], v[7]), v_scale);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (j < n) {
+            const RowMeta rm = rows[ra + j];
+            vpool[page_of(rm) + at + rm.pos % kPage] = KvStore<KVT>::one(v[j], v_scale);
+          }
+      }
+    }
+    return;
+  }
+  const int row = blockIdx.x / n_parts, part_id = blockIdx.x % n_parts;
   const float* pr = part + (int64_t)row * ncols;
-  const int page = bt[(int64_t)rm.slot * bt_stride + rm.pos / kPage];
-  const int slot = rm.pos % kPage;
-  const int64_t page_base = (int64_t)page * page_stride;
-  const float2* cs = rope_cs + (int64_t)rm.pos * half;
-
-  // blockIdx.y splits the row's work across gridDim.y groups.
-  const int part_id = blockIdx.y, n_parts = gridDim.y;
   const int quads_per_head = half / 4;
   const int n_quads = (n_q_heads + n_kv_heads) * quads_per_head;
-  for (int qd = part_id * kRowThreads + threadIdx.x; qd < n_quads; qd += n_parts * kRowThreads) {
+  const int n_all = n_quads + (v_rows == 1 ? n_kv_heads * head_dim / 4 : 0);
+  for (int qd = part_id * kRowThreads + threadIdx.x; qd < n_all; qd += n_parts * kRowThreads) {
+    if (qd >= n_quads) {  // four dims of v
+      const int c = (qd - n_quads) * 4;
+      const float4 v = add_splits4(*(const float4*)(pr + vcol0 + c), pr + slab + vcol0 + c, slab,
+                                   splits - 1);
+      const RowMeta rm = rows[row];
+      KVT* dst = vpool + page_of(rm) + (int64_t)c * kPage + rm.pos % kPage;
+      dst[0] = KvStore<KVT>::one(v.x, v_scale);
+      dst[kPage] = KvStore<KVT>::one(v.y, v_scale);
+      dst[2 * kPage] = KvStore<KVT>::one(v.z, v_scale);
+      dst[3 * kPage] = KvStore<KVT>::one(v.w, v_scale);
+      continue;
+    }
     const int hh = qd / quads_per_head, i = (qd % quads_per_head) * 4;
     const int c0 = hh * head_dim + i, c1 = c0 + half;
     float4 a = add_splits4(*(const float4*)(pr + c0), pr + slab + c0, slab, splits - 1);
@@ -193,6 +295,8 @@ __global__ __launch_bounds__(kRowThreads) void qkv_rope_kv_kernel(
       a = make_float4(a.x * r * ga.x, a.y * r * ga.y, a.z * r * ga.z, a.w * r * ga.w);
       b = make_float4(b.x * r * gb.x, b.y * r * gb.y, b.z * r * gb.z, b.w * r * gb.w);
     }
+    const RowMeta rm = rows[row];
+    const float2* cs = rope_cs + (int64_t)rm.pos * half;
     const float4 t01 = *(const float4*)(cs + i), t23 = *(const float4*)(cs + i + 2);
     const float4 ra = make_float4(a.x * t01.x - b.x * t01.y, a.y * t01.z - b.y * t01.w,
                                   a.z * t23.x - b.z * t23.y, a.w * t23.z - b.w * t23.w);
@@ -203,17 +307,10 @@ __global__ __launch_bounds__(kRowThreads) void qkv_rope_kv_kernel(
       Pack4<T>::store(dst + i, ra);
       Pack4<T>::store(dst + i + half, rb);
     } else {
-      KVT* dst = kpool + page_base + ((int64_t)(hh - n_q_heads) * kPage + slot) * head_dim;
+      KVT* dst = kpool + page_of(rm) + ((int64_t)(hh - n_q_heads) * kPage + rm.pos % kPage) * head_dim;
       KvStore<KVT>::store4(dst + i, ra, k_scale);
       KvStore<KVT>::store4(dst + i + half, rb, k_scale);
     }
-  }
-  const int vcol0 = (n_q_heads + n_kv_heads) * head_dim;
-  for (int idx = part_id * kRowThreads + threadIdx.x; idx < n_kv_heads * head_dim;
-       idx += n_parts * kRowThreads) {
-    const float v = add_splits1(0.f, pr + vcol0 + idx, slab, splits);
-    const int g = idx / head_dim, dd = idx % head_dim;
-    vpool[page_base + ((int64_t)g * head_dim + dd) * kPage + slot] = KvStore<KVT>::one(v, v_scale);
   }
 }
 
@@ -265,23 +362,42 @@ __device__ __forceinline__ void argmax_merge(float& v, int& i, float v2, int i2)
   }
 }
 
-// One work group of 1024 threads per row.  Ties go to the lowest index.
-__global__ __launch_bounds__(1024) void argmax_kernel(int V, const float* __restrict__ logits,
-                                                      int32_t* __restrict__ tokens) {
+// One work group of up to 1024 threads per (chunk, row); a chunk is `span` tokens
+// (a multiple of 4).  Ties go to the lowest index.  With part, the chunk's best
+// goes to part[row][chunk]; otherwise (one chunk) to tokens.
+__global__ __launch_bounds__(1024) void argmax_kernel(int V, int span,
+                                                      const float* __restrict__ logits,
+                                                      int32_t* __restrict__ tokens,
+                                                      float2* __restrict__ part) {
   __shared__ float sv[16];
   __shared__ int si[16];
-  const float* lr = logits + (int64_t)blockIdx.x * V;
+  const float* lr = logits + (int64_t)blockIdx.y * V;
+  const int i0 = blockIdx.x * span, i1 = i0 + min(span, V - i0), n = blockDim.x;
   float best = -INFINITY;
   int bi = 0x7FFFFFFF;
-  const int v4 = (((uintptr_t)lr & 15) == 0) ? V / 4 : 0;
-  for (int q = threadIdx.x; q < v4; q += 1024) {
-    const float4 v = *(const float4*)(lr + q * 4);
+  const int v4 = (((uintptr_t)lr & 15) == 0) ? i1 / 4 : i0 / 4;  // whole float4s end here
+  int q = i0 / 4 + threadIdx.x;
+  for (; q + 3 * n < v4; q += 4 * n) {
+    float4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = *(const float4*)(lr + (int64_t)(q + u * n) * 4);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int at = (q + u * n) * 4;
+      argmax_merge(best, bi, v[u].x, at);
+      argmax_merge(best, bi, v[u].y, at + 1);
+      argmax_merge(best, bi, v[u].z, at + 2);
+      argmax_merge(best, bi, v[u].w, at + 3);
+    }
+  }
+  for (; q < v4; q += n) {
+    const float4 v = *(const float4*)(lr + (int64_t)q * 4);
     argmax_merge(best, bi, v.x, q * 4);
     argmax_merge(best, bi, v.y, q * 4 + 1);
     argmax_merge(best, bi, v.z, q * 4 + 2);
     argmax_merge(best, bi, v.w, q * 4 + 3);
   }
-  for (int i = v4 * 4 + threadIdx.x; i < V; i += 1024) argmax_merge(best, bi, lr[i], i);
+  for (int i = v4 * 4 + threadIdx.x; i < i1; i += n) argmax_merge(best, bi, lr[i], i);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     const float v2 = __shfl_xor(best, o, 64);
@@ -294,9 +410,32 @@ __global__ __launch_bounds__(1024) void argmax_kernel(int V, const float* __rest
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < 16; ++w) argmax_merge(best, bi, sv[w], si[w]);
-    tokens[blockIdx.x] = (bi == 0x7FFFFFFF) ? 0 : bi;
+    for (int w = 1; w < n / 64; ++w) argmax_merge(best, bi, sv[w], si[w]);
+    if (part)
+      part[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = make_float2(best, __int_as_float(bi));
+    else
+      tokens[blockIdx.y] = (bi == 0x7FFFFFFF) ? 0 : bi;
   }
+}
+
+// One wave per row merges up to 64 chunks.
+__global__ __launch_bounds__(64) void argmax_merge_kernel(int chunks,
+                                                          const float2* __restrict__ part,
+                                                          int32_t* __restrict__ tokens) {
+  float best = -INFINITY;
+  int bi = 0x7FFFFFFF;
+  if ((int)threadIdx.x < chunks) {
+    const float2 p = part[(int64_t)blockIdx.x * chunks + threadIdx.x];
+    best = p.x;
+    bi = __float_as_int(p.y);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const float v2 = __shfl_xor(best, o, 64);
+    const int i2 = __shfl_xor(bi, o, 64);
+    argmax_merge(best, bi, v2, i2);
+  }
+  if (threadIdx.x == 0) tokens[blockIdx.x] = (bi == 0x7FFFFFFF) ? 0 : bi;
 }
 
 __global__ void bt_deltas_kernel(int n, const BtDelta* __restrict__ d, int32_t* __restrict__ bt,
@@ -316,6 +455,9 @@ __global__ void rope_table_kernel(int max_pos, int half, double base, float2* __
   }
 }
 
+// Threads of a row's work group: one float4 each, up to 1024.
+inline int row_threads(int d) { return std::max(64, std::min(1024, (d / 4 + 63) / 64 * 64)); }
+
 inline int grid_for(int64_t n, int block) {
   return (int)std::min<int64_t>((n + block - 1) / block, 65536);
 }
@@ -326,19 +468,27 @@ hipError_t launch_embed_norm(int dtype, int M, int d, int vocab, const int32_t* 
                              const void* embed,
                              const float* gain, float eps, float* x, void* h, hipStream_t stream) {
   if (M == 0) return hipSuccess;
-  if (dtype == 1)
-    embed_norm_kernel<uint16_t, uint16_t><<<M, kRowThreads, 0, stream>>>(
-        d, vocab, tokens, (const uint16_t*)embed, gain, eps, x, (uint16_t*)h);
-  else
-    embed_norm_kernel<float, float><<<M, kRowThreads, 0, stream>>>(
-        d, vocab, tokens, (const float*)embed, gain, eps, x, (float*)h);
+  const int elem = dtype == 1 ? 2 : 4;
+  const bool vec = d % 4 == 0 && (uintptr_t)embed % (4 * elem) == 0 && (uintptr_t)gain % 16 == 0;
+  const int threads = vec ? row_threads(d) : kRowThreads;
+#define PDEC_EMBED(KERNEL_, T_)                                                               \
+  KERNEL_<T_, T_><<<M, threads, 0, stream>>>(d, vocab, tokens, (const T_*)embed, gain, eps, x, \
+                                             (T_*)h)
+  if (dtype == 1) {
+    if (vec) PDEC_EMBED(embed_norm_kernel, uint16_t);
+    else PDEC_EMBED(embed_norm_any_kernel, uint16_t);
+  } else {
+    if (vec) PDEC_EMBED(embed_norm_kernel, float);
+    else PDEC_EMBED(embed_norm_any_kernel, float);
+  }
+#undef PDEC_EMBED
   return hipGetLastError();
 }
 
 hipError_t launch_resid_norm(int dtype, int M, int d, const float* part, int splits, float* x,
                              const float* gain, float eps, void* h, hipStream_t stream) {
   if (M == 0) return hipSuccess;
-  const int threads = std::max(64, std::min(1024, (d / 4 + 63) / 64 * 64));
+  const int threads = row_threads(d);
   if (dtype == 1)
     resid_norm_kernel<uint16_t><<<M, threads, 0, stream>>>(M, d, part, splits, x, gain, eps,
                                                            (uint16_t*)h);
@@ -356,16 +506,18 @@ hipError_t launch_qkv_rope_kv(int dtype, int kv_fp8, float k_scale, float v_scal
                               const float* q_gain, const float* k_gain, float eps,
                               hipStream_t stream) {
   if (M == 0) return hipSuccess;
-  // Enough groups per row that every thread has at most one (q or k) quad,
-  // so no group runs a second, mostly idle pass; small batches take more
-  // groups per row to fill the GPU.
-  const int n_quads = (n_q_heads + n_kv_heads) * (head_dim / 8);
-  const dim3 grid(M, std::max(M >= 64 ? 2 : 8, (n_quads + kRowThreads - 1) / kRowThreads));
+  // One quad per thread.  From 64 rows on v takes work groups of its own, 16
+  // rows each; below that a row's v quads run beside its q and k quads.
+  const int v_rows = M >= 64 ? 16 : 1;
+  const int n_quads = (n_q_heads + n_kv_heads) * (head_dim / 8) +
+                      (v_rows == 1 ? n_kv_heads * head_dim / 4 : 0);
+  const int n_parts = (n_quads + kRowThreads - 1) / kRowThreads;
+  const int grid = M * n_parts + (v_rows == 16 ? (M + 15) / 16 * n_kv_heads : 0);
 #define PDEC_QKV(T_, KVT_)                                                                   \
   qkv_rope_kv_kernel<T_, KVT_><<<grid, kRowThreads, 0, stream>>>(                             \
       M, head_dim, n_q_heads, n_kv_heads, part, splits, rows, rope_cs, block_table, bt_stride, \
       (T_*)q_out, (KVT_*)k_pages, (KVT_*)v_pages, page_stride_elems, q_gain, k_gain, eps,     \
-      k_scale, v_scale)
+      k_scale, v_scale, n_parts, v_rows)
   if (dtype == 1 && kv_fp8)
     PDEC_QKV(uint16_t, uint8_t);
   else if (dtype == 1)
@@ -405,9 +557,22 @@ hipError_t launch_gather_rows(int n, const int32_t* idx, const void* src, int64_
   return hipGetLastError();
 }
 
-hipError_t launch_argmax(int B, int V, const float* logits, int32_t* tokens, hipStream_t stream) {
+hipError_t launch_argmax(int B, int V, const float* logits, int32_t* tokens, void* scratch,
+                         int64_t scratch_bytes, hipStream_t stream) {
   if (B == 0) return hipSuccess;
-  argmax_kernel<<<B, 1024, 0, stream>>>(V, logits, tokens);
+  // One work group per row reads a 513 KB row at one CU's rate (20 us at any
+  // batch up to 64); chunks of a row on several CUs and a merge of their bests
+  // take 11 (6 and 5).  From 128 rows on the rows alone fill the GPU.
+  const int chunks = V < 32768 ? 1 : B < 128 ? std::min(64, kArgmaxPairs / B) : 1;
+  if (chunks > 1 && scratch && (int64_t)B * chunks * (int64_t)sizeof(float2) <= scratch_bytes) {
+    const int span = (int)((((int64_t)V + chunks - 1) / chunks + 3) / 4 * 4);
+    const int used = (V - 1) / span + 1;
+    float2* part = (float2*)scratch;
+    argmax_kernel<<<dim3(used, B), 256, 0, stream>>>(V, span, logits, tokens, part);
+    argmax_merge_kernel<<<B, 64, 0, stream>>>(used, part, tokens);
+    return hipGetLastError();
+  }
+  argmax_kernel<<<dim3(1, B), 1024, 0, stream>>>(V, V, logits, tokens, nullptr);
   return hipGetLastError();
 }
 

@@ -1,0 +1,79 @@
+"""Branches of the per-row kernels.
+
+Greedy sampling: rows cut into chunks against whole rows (by vocabulary and
+batch), ties across chunk edges to the lowest index, NaN and -inf, rows that do
+not start 16-byte aligned; exact against numpy.
+
+V pages: passes of 64 rows and more write V 16 rows at a time (eight slots of a
+page with one store where they line up), smaller ones a row at a time.  The same
+tokens appended in passes of both kinds leave the same layer-0 pages: K and V
+depend there on the token's own row alone, so the values differ by the summation
+order of one fp32 product, at most one step of the storage type.
+"""
+
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _engine(shape, dtype, **kw):
+    import paper_2609_36899_amd as P
+    from workload import make_weights
+    w = P.weights_to_device(make_weights(shape, seed=3, bf16=dtype == P.BF16), dtype)
+    per_tok = P.kv_bytes_per_token(shape, dtype, kw.get("kv_fp8"))
+    return P.Engine(shape, w, dtype, 64 * 16 * per_tok, max_seqs=4, max_seq_len=512, max_batch=4,
+                    max_chunk=160, **kw)
+
+
+@pytest.mark.parametrize("vocab,offset", [(1024, 0), (32768, 0), (32771, 0), (128256, 0), (128256, 1)])
+def test_greedy_chunks(vocab, offset):
+    import paper_2609_36899_amd as P
+    from workload import TINY
+    E = _engine(dataclasses.replace(TINY, n_layers=1, d_model=64, ffn_dim=64, vocab=vocab), P.F32)
+    rng = np.random.default_rng(vocab)
+    for B in (1, 5, 64, 127, 128):
+        z = rng.standard_normal((B, vocab)).astype(np.float32)
+        z[0] = np.round(z[0])                      # ties everywhere
+        if B > 4:
+            z[1] = -np.inf
+            z[2, ::2] = np.nan
+            z[3] = 1.0                             # all equal
+            z[4] = -np.inf
+            z[4, vocab - 1] = -3.0
+        want = [int(np.argmax(np.where(np.isnan(r), -np.inf, r))) for r in z]
+        buf = torch.empty(offset + B * vocab, device="cuda")
+        zd = buf[offset:].view(B, vocab)
+        zd.copy_(torch.from_numpy(z))
+        tok = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+        E.sample(zd, tok)
+        np.testing.assert_array_equal(tok.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("kind", ["f32", "bf16", "fp8"])
+@pytest.mark.parametrize("before", [0, 5, 8, 16, 27])
+def test_v_rows_match_single_rows(kind, before):
+    import paper_2609_36899_amd as P
+    from workload import SMALL_BF16, TINY, random_tokens
+    shape, dtype = (TINY, P.F32) if kind == "f32" else (SMALL_BF16, P.BF16)
+    toks = random_tokens(before + 139, shape.vocab, 5)
+    pages = []
+    for chunk in (160, 16):  # one pass of 139 rows; passes of at most 16
+        E = _engine(shape, dtype, kv_fp8=(0.02, 0.03) if kind == "fp8" else None)
+        s = E.kv_alloc(0)
+        if before:
+            E.kv_append_prefix(s, toks[:before], chunk_tokens=16)
+        E.kv_append_prefix(s, toks[before:], chunk_tokens=chunk)
+        at = torch.arange(len(toks), device="cuda")
+        pg = torch.from_numpy(E.kv_block_table(s)).cuda().long()[at // 16]
+        view = lambda t: (t.view(torch.float8_e4m3fn) if kind == "fp8" else t).float()
+        pages.append((view(E.k_pages(0))[pg, :, at % 16], view(E.v_pages(0))[pg, :, :, at % 16]))
+    step = {"f32": 2.0 ** -20, "bf16": 2.0 ** -7, "fp8": 2.0 ** -3}[kind]
+    for a, b in zip(*pages):
+        floor = 2.0 ** -9 if kind == "fp8" else 1e-6  # the smallest code
+        assert torch.all((a - b).abs() <= step * torch.maximum(a.abs(), b.abs()) + floor)
+        assert (a != b).float().mean() < (1.0 if kind == "f32" else 0.01)
+        assert a.abs().max() > 0
