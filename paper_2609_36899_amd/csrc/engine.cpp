@@ -269,7 +269,11 @@ size_t part_elems_for(const pdec_model_cfg* c, int64_t rows_cap) {
                             {2 * c->ffn_dim, c->d_model},
                             {c->d_model, c->ffn_dim}};
   size_t best = 0;
-  for (int64_t m = 1; m <= rows_cap; ++m) {
+  // Above 256 rows the bf16 plans change at multiples of 64 rows only, the fp32
+  // ones at multiples of 32, so the largest product lies at one of them.
+  const int64_t step = c->dtype == PDEC_BF16 ? 64 : 32;
+  for (int64_t m = 1; m <= rows_cap;
+       m = m < 256 ? m + 1 : m < rows_cap ? std::min(m + step, rows_cap) : m + 1) {
     for (int i = 0; i < 4; ++i) {
       int ks;
       const int S = gemm_plan_splits(c->dtype, (int)m, shapes[i][0], shapes[i][1], &ks, i == 2);

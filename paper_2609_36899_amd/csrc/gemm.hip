@@ -13,7 +13,7 @@
 // 10-25% slower.
 //
 // Kernels by batch rows: the streaming kernel (up to 32 rows, weights straight
-// into registers), the 128- and 256-row LDS tiles (up to 256 rows), and the
+// into registers), the 64- to 256-row LDS tiles, and the
 // 256 x 256 tile above that.  When the column tiles alone cannot fill 256 CUs
 // the K axis is split and the fp32 partial sums are reduced in a fixed order
 // by the next kernel.
@@ -247,47 +247,58 @@ __global__ __launch_bounds__(64 * kStripWaves) void gemm_bf16_strip(
     if (4 * q4 + rr < M && col < gr.col_end) out[(int64_t)(4 * q4 + rr) * N + col] = acc[rr];
 }
 
-// Larger batches (M > 32): (64 WM) x 128 output tiles, 2 WM waves in a WM x 2
-// grid of 64 x 64 sub-tiles.  Per k-step of 64 the A tile and the W tile are
-// staged once through LDS and each is shared by the waves that need it.  The
-// tiles travel from memory straight into LDS (16-byte LDS-DMA loads, no
-// register staging), through a ring of three stages: while step it is
-// computed, steps it+1 and it+2 are in flight.  One barrier per step: after
-// it, every wave has finished step it-1, whose stage then takes step it+2.
+// Larger batches (M > 32): ROWS x 128 output tiles, waves in a (ROWS / 16 MT) x 2
+// grid of 16 MT x 64 sub-tiles (64 x 64, and 32 x 64 for the 64-row tile).  Per
+// k-step of 64 the A tile and the W tile are staged once through LDS and each is
+// shared by the waves that need it.  The tiles travel from memory straight into
+// LDS (16-byte LDS-DMA loads, no register staging), through a ring of D stages:
+// while step it is computed, steps it+1 .. it+D-1 are in flight.  One barrier per
+// step: after it, every wave has finished step it-1, whose stage then takes step
+// it+D-1.  Up to 64 rows the weight stream is the bound and what is in flight
+// sets its rate: two stages of 16 KiB per CU gave gate/up 5.0 TB/s at 64 rows
+// (45.8 us), five (D = 6, 24 KiB stages) 5.7 (40.9).  From 128 rows on a fourth
+// stage measured level or slower.
 // The W tile (one packed group, 2 k-blocks x 8 strips) is one contiguous
 // 16 KiB run in HBM, copied in packed order (fragment reads from LDS are
 // linear, hence free of bank conflicts) with the non-temporal hint, so the
-// weight stream does not push the re-read A tiles out of L2; the A tile is row-major with its
-// 16-byte chunks XOR-swizzled by
-// row (the swizzle is applied to the source address, as the DMA writes each
-// wave's 64 chunks contiguously).  WM = 4 covers 256 rows, so up to that
-// batch size W is read from HBM exactly once per step.  Larger batches take
-// several M-blocks, laid out so the M-blocks of one column tile are
-// dispatched back to back (ids L and L+8 share an XCD).
+// weight stream does not push the re-read A tiles out of L2; the A tile is
+// row-major with its 16-byte chunks XOR-swizzled by row (the swizzle is applied
+// to the source address, as the DMA writes each wave's 64 chunks contiguously).
+// Up to 256 rows one tile covers the batch, so W is read from HBM exactly once
+// per step.  Larger batches take several M-blocks, laid out so the M-blocks of one
+// column tile are dispatched back to back (ids L and L+8 share an XCD).
 // GLU (gate and up as the two segments of w, N = F, no K split): column tile
 // v holds half v % 2 of group v / 2 of both matrices, its eight strips
 // staged as gate, up, gate, up, ... so that each wave's four strips are two
 // (gate, up) pairs of the same columns; the epilogue writes silu(gate) * up
 // as bf16 to u [M][F].
-template <int WM, bool GLU>
-__global__ __launch_bounds__(128 * WM) void gemm_bf16_tile(int M, int N, int K, int k_split,
+template <int ROWS, int MT, int D, bool GLU>
+__global__ __launch_bounds__(8 * ROWS / MT) void gemm_bf16_tile(int M, int N, int K, int k_split,
                                                           int n_mb, int n_nb,
                                                           const uint16_t* __restrict__ A,
                                                           int64_t lda, WSegs w,
                                                           float* __restrict__ out,
                                                           uint16_t* __restrict__ glu_out) {
-  constexpr int MT = 4, NT = 4, D = 3;
-  constexpr int THREADS = 128 * WM, ROWS = 64 * WM;
-  constexpr int ACH = ROWS * 8 / THREADS;  // A chunks per thread per stage (4)
-  constexpr int WCH = 1024 / THREADS;      // W chunks per thread per stage (16 KiB tile)
-  constexpr int LPS = ACH + WCH;           // loads per thread per stage
-  constexpr int SA = ROWS * 64, STAGE = SA + 128 * 64;
+  constexpr int NT = 4;
+  constexpr int THREADS = 8 * ROWS / MT;           // (ROWS / 16 MT) x 2 waves
+  constexpr int ACH = ROWS * 8 / THREADS;          // A chunks per thread per stage (MT)
+  constexpr int WCH = (1024 + THREADS - 1) / THREADS;  // W chunks per thread (16 KiB tile)
+  constexpr int LPS = ACH + WCH;                   // loads per thread per stage
+  // 384 threads: the last W load of the waves past the tile repeats chunks into
+  // padding, so that every wave has the same number of loads in flight.
+  constexpr int SA = ROWS * 64, STAGE = SA + WCH * THREADS * 8;
+  static_assert(D >= 3 && D <= 6 && STAGE * 2 * D <= 160 * 1024, "stages fit the LDS");
   // One array per stage: the compiler then tells the stages' LDS apart and
   // does not wait for every DMA in flight before reading a landed stage.
   __shared__ __attribute__((aligned(16))) uint16_t lds0[STAGE];
   __shared__ __attribute__((aligned(16))) uint16_t lds1[STAGE];
   __shared__ __attribute__((aligned(16))) uint16_t lds2[STAGE];
-  auto stage_ptr = [&](int b) -> uint16_t* { return b == 0 ? lds0 : b == 1 ? lds1 : lds2; };
+  __shared__ __attribute__((aligned(16))) uint16_t lds3[D > 3 ? STAGE : 8];
+  __shared__ __attribute__((aligned(16))) uint16_t lds4[D > 4 ? STAGE : 8];
+  __shared__ __attribute__((aligned(16))) uint16_t lds5[D > 5 ? STAGE : 8];
+  auto stage_ptr = [&](int b) -> uint16_t* {
+    return b == 0 ? lds0 : b == 1 ? lds1 : b == 2 ? lds2 : b == 3 ? lds3 : b == 4 ? lds4 : lds5;
+  };
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int c16 = lane & 15, q4 = lane >> 4;
   const int L = blockIdx.x;
@@ -317,7 +328,7 @@ __global__ __launch_bounds__(128 * WM) void gemm_bf16_tile(int M, int N, int K, 
   const uint16_t* wsrc[WCH];
 #pragma unroll
   for (int j = 0; j < WCH; ++j) {
-    const int id = j * THREADS + tid;
+    const int id = (j * THREADS + tid) & 1023;
     if constexpr (GLU) {  // staged strip sp: strip 4 h + sp / 2 of gate (sp even) or up
       const int kb = id >> 9, sp = (id >> 6) & 7, ln = id & 63;
       wsrc[j] = (const uint16_t*)w.ptr[sp & 1] + (int64_t)(nb >> 1) * kGroupCols * K +
@@ -331,7 +342,7 @@ __global__ __launch_bounds__(128 * WM) void gemm_bf16_tile(int M, int N, int K, 
   for (int t = 0; t < MT; ++t)
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int ra = wm * 64 + t * 16 + c16, cc = h * 4 + q4;
+      const int ra = wm * 16 * MT + t * 16 + c16, cc = h * 4 + q4;
       aoff[t][h] = ra * 64 + ((cc ^ (ra & 7)) * 8);
     }
 
@@ -406,7 +417,7 @@ __global__ __launch_bounds__(128 * WM) void gemm_bf16_tile(int M, int N, int K, 
         const int col = gr.col0 + (2 * wn + p) * 16 + c16;
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) {
-          const int row = m_blk + wm * 64 + i * 16 + 4 * q4 + rr;
+          const int row = m_blk + wm * 16 * MT + i * 16 + 4 * q4 + rr;
           if (row < M && col < gr.col_end)
             glu_out[(int64_t)row * N + col] =
                 f32_to_bf16(silu_mul(acc[i][2 * p][rr], acc[i][2 * p + 1][rr]));
@@ -421,7 +432,7 @@ __global__ __launch_bounds__(128 * WM) void gemm_bf16_tile(int M, int N, int K, 
         const int col = gr.col0 + wn * 64 + j * 16 + c16;
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) {
-          const int row = m_blk + wm * 64 + i * 16 + 4 * q4 + rr;
+          const int row = m_blk + wm * 16 * MT + i * 16 + 4 * q4 + rr;
           if (row < M && col < gr.col_end) o[(int64_t)row * N + col] = acc[i][j][rr];
         }
       }
@@ -734,20 +745,69 @@ __global__ __launch_bounds__(64) void gemm_f32_rows(int M, int N, int K,
 //  * M <= 32: the streaming kernel (two strips per wave, ring depth 2), or the
 //    strip kernel (strip_form);
 //    6.0-6.6 TB/s of weights up to M = 16;
-//  * larger M: the 128 x 128 tile (M <= 128) or 256 x 128 tile, and above
-//    256 rows the 256 x 256 tile where its grid fills the GPU.
+//  * larger M: the 64- to 256-row tiles (plan_tile), and above 256 rows the
+//    256 x 256 tile where its grid fills the GPU.
 constexpr int kStreamMaxRows = 32;
 
-// Rows per tile: 128 (4 waves) up to 128-row batches, 256 (8 waves) beyond,
-// so W is read once per step for batches up to 256.  Above 256 rows the
-// 256 x 256 tile (two column groups per work group).
-int tile_rows(int M) { return M <= 128 ? 128 : 256; }
-// The 256 x 256 tile is taken only where its grid alone fills the GPU
-// (gate/up and the LM head at any M > 256, qkv only past ~2300 rows): where
-// it would need more K splits than the 256 x 128 tile (o, down, qkv at
-// 384-1024 rows) the extra partial traffic made it 5-45% slower.
-bool wide_tiles(int M, int64_t groups) {
-  return M > 256 && ((groups + 1) / 2) * ((M + 255) / 256) >= 224;
+// Row tiles of the 128-column kernel: 64, 128, 192 or 256 rows, so that up to 256
+// rows W is read once per step by the smallest tile that holds the batch.
+// Measured (us, against the tile the batch took before, 128 rows up to 128 and 256
+// above): gate/up 40.9 / 45.8 at 64 rows, 59.1 / 64.2 at 192, down 36.6 / 39.9 at
+// 160.  Up to 64 rows a long K split over the grid (down: 28 k-steps of 64 per
+// work group) is 2-3% faster on the 128-row tile.
+//
+// Above 256 rows (kRowStep steps) the tile and the K splits are chosen together.
+// The grid rarely fills whole rounds of the 256 CUs, and what a round costs is
+// close to linear in the tile's rows; over 300-2048 rows of qkv, o and down of the
+// 8B shape, and all three tiles, the times follow within about 5%
+//   (24 + 0.165 rows) K / 4096 us per full round, a last round filled by p
+//   counting 0.58 + 0.4 p, divided by the splits,
+// plus the splits' partial sums written and read at about 5 TB/s.  Against
+// 256-row tiles with the splits planned alone: qkv 97.7 / 108.3 at 1400 rows (two
+// rounds of 192 instead of one and an eighth of 256), 44.6 / 52.1 at 600 (128-row
+// tiles), down 174 / 191 at 1400 and 60.7 / 68.3 at 300.
+//
+// The 256 x 256 tile enters the same comparison, unsplit and at 111 us a round,
+// where its grid alone nearly fills the GPU (gate/up and the LM head at any M >
+// 256): where it would need more K splits than the 256 x 128 tile (o, down, qkv at
+// 384-1024 rows) the extra partial traffic made it 5-45% slower.  Gate/up of the
+// 14B shape at 300 rows, 272 wide tiles, is one it loses: 273 us against 183.
+struct TilePlan {
+  int rows, splits;  // rows of the 128-column tile
+  bool wide;         // the 256 x 256 tile instead (splits = 1)
+};
+constexpr int kRowStep = 64;  // above 256 rows the plan is the same within a step
+// Rounds of 256 work groups that n cost.
+double grid_rounds(int64_t n) {
+  return (double)(n / 256) + (n % 256 ? 0.58 + 0.4 * (double)(n % 256) / 256 : 0.0);
+}
+TilePlan plan_tile(int M, int K, int64_t groups, bool glu, bool may_widen) {
+  if (M <= 256) {
+    // One round of work groups: a partial second one costs 15-30%.
+    const int splits = (int)std::min<int64_t>(8, std::max<int64_t>(1, 256 / groups));
+    const int rows = M <= 64 && (glu || splits == 1 || K < 8192) ? 64
+                     : M <= 128                                  ? 128
+                     : M <= 192                                  ? 192
+                                                                 : 256;
+    return {rows, splits, false};
+  }
+  const int m = (M + kRowStep - 1) / kRowStep * kRowStep;
+  TilePlan best{256, 1, false};
+  double least = 1e30;
+  const int64_t wide = (groups + 1) / 2 * ((m + 255) / 256);
+  if (may_widen && wide >= 224) {
+    least = grid_rounds(wide) * 111 * K / 4096;
+    best.wide = true;
+  }
+  for (int rows = 256; rows >= 128; rows -= 64) {
+    const int64_t tiles = groups * ((m + rows - 1) / rows);
+    for (int s = 1; s <= 8 && (s == 1 || tiles * s <= 1024); ++s) {
+      const double us = grid_rounds(tiles * s) * (24 + 0.165 * rows) * K / 4096 / s +
+                        (s - 1) * (double)m * (double)groups * kGroupCols * 8 / 5e6;
+      if (us < least * (best.wide ? 0.95 : 0.99)) least = us, best = {rows, s, false};
+    }
+  }
+  return best;
 }
 
 // Where the strip kernel takes a projection: its strips fit the 256 CUs once
@@ -777,28 +837,10 @@ int gemm_plan_splits(int dtype, int M, int N, int K, int* k_split, bool glu) {
       *k_split = K;
       return 1;
     }
-    if (wide_tiles(M, groups)) groups = ((groups + 1) / 2) * ((M + 255) / 256);
-    else if (M > kStreamMaxRows) groups *= (M + tile_rows(M) - 1) / tile_rows(M);
-    // Measured on the 8B shapes with weights streamed from HBM: the best
-    // split count fills one round of work groups on the 256 CUs (a partial
-    // second round costs 15-30%).
-    s = (int)std::max<int64_t>(1, 256 / groups);
-    s = std::min(s, 8);
-    // Above 256 rows (prefill chunks, large batches) with a long K (the down
-    // projection), a grid of 129-255 work groups fills one round poorly; up
-    // to 4 splits are weighed by rounds per unit of work,
-    // ceil(groups * s / 256) / s, ties to fewer splits.  Measured at 640-1536
-    // rows this picked the best count every time (1242 rows: 160 groups,
-    // 3 splits, 142 against 189 us).  With K = 4096 the shorter split loops
-    // and the partials cost more than the rounds save, so those keep the
-    // rule above.
-    if (M > 256 && groups < 256 && K >= 8192) {
-      double best = 1e30;
-      for (int c = 1; c <= 4; ++c) {
-        const double cost = (double)((groups * c + 255) / 256) / c;
-        if (cost < best - 1e-9) best = cost, s = c;
-      }
-    }
+    if (M > kStreamMaxRows)
+      s = plan_tile(M, K, groups, glu, true).splits;
+    else  // one round of work groups, as above
+      s = (int)std::min<int64_t>(8, std::max<int64_t>(1, 256 / groups));
   } else {
     const int64_t groups = (int64_t)((N + 63) / 64) * ((M + 31) / 32);
     if (f32_rows_shape(M, K))
@@ -829,8 +871,6 @@ template <bool GLU>
 hipError_t launch_gemm_bf16(int M, int N, int K, const uint16_t* a, int64_t lda, const WSegs& w,
                             int n_groups, float* out, uint16_t* glu_out, int splits, int k_split,
                             hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  // Plain matrices given as several segments (q|k|v) keep the 256 x 128 tile.
-  const bool wide = wide_tiles(M, n_groups) && (GLU || w.n_seg == 1);
   if constexpr (!GLU) {
     if (splits == 1 && strip_form(M, K, n_groups))
       return launch_timed(gemm_bf16_strip, dim3(n_groups * 8), dim3(64 * kStripWaves), stream,
@@ -844,21 +884,26 @@ hipError_t launch_gemm_bf16(int M, int N, int K, const uint16_t* a, int64_t lda,
     return launch_timed(gemm_bf16_stream<2, 2, GLU>, grid, dim3(256), stream, ev_start, ev_stop,
                         M, N, K, k_split, a, lda, w, out, glu_out);
   }
-  if (wide) {
+  // Plain matrices given as several segments (q|k|v) keep the 128-column tile.
+  const TilePlan plan = plan_tile(M, K, n_groups, GLU, splits == 1 && (GLU || w.n_seg == 1));
+  if (plan.wide) {
     // GLU: n_groups counts half-groups; a wide column tile is one whole group.
     const int n_mb = (M + 255) / 256, n_nb = GLU ? n_groups / 2 : (n_groups + 1) / 2;
     const dim3 grid(((n_nb + 7) / 8) * 8 * n_mb, 1, splits);
     return launch_timed(gemm_bf16_wide<GLU>, grid, dim3(512), stream, ev_start, ev_stop, M, N, K,
                         k_split, n_mb, n_nb, n_groups, a, lda, w, out, glu_out);
   }
-  const int rows = tile_rows(M);
+  const int rows = plan.rows;
   const int n_mb = (M + rows - 1) / rows, n_nb = n_groups;
   const dim3 grid(((n_nb + 7) / 8) * 8 * n_mb, 1, splits);
-  if (rows == 128)
-    return launch_timed(gemm_bf16_tile<2, GLU>, grid, dim3(256), stream, ev_start, ev_stop, M, N,
-                        K, k_split, n_mb, n_nb, a, lda, w, out, glu_out);
-  return launch_timed(gemm_bf16_tile<4, GLU>, grid, dim3(512), stream, ev_start, ev_stop, M, N, K,
-                      k_split, n_mb, n_nb, a, lda, w, out, glu_out);
+#define PDEC_TILE(ROWS_, MT_, D_)                                                              \
+  return launch_timed(gemm_bf16_tile<ROWS_, MT_, D_, GLU>, grid, dim3(8 * ROWS_ / MT_), stream, \
+                      ev_start, ev_stop, M, N, K, k_split, n_mb, n_nb, a, lda, w, out, glu_out)
+  if (rows == 64) PDEC_TILE(64, 2, 6);
+  if (rows == 128) PDEC_TILE(128, 4, 3);
+  if (rows == 192) PDEC_TILE(192, 4, 3);
+  PDEC_TILE(256, 4, 3);
+#undef PDEC_TILE
 }
 
 }  // namespace

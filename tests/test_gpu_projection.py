@@ -61,6 +61,14 @@ def test_bf16_8b_shapes_sampled_rows(M, N, K):
     _run(M, N, K, seed=N + M, rows=rows)
 
 
+@pytest.mark.parametrize("M", [33, 63, 64, 65, 191, 192, 193, 320, 384, 385, 600, 641])
+@pytest.mark.parametrize("N,K", [(1412, 576), (4096, 8192), (6144, 128)])
+def test_bf16_row_tiles(M, N, K):
+    """Edges of the 64-, 128-, 192- and 256-row tiles, up to 256 rows one tile,
+    above it the planner's choice of tile and splits; 2 to 128 k-steps."""
+    _run(M, N, K, seed=M + K, rows=sorted({0, 31, 32, M // 2, M - 2, M - 1} | {min(M - 1, r) for r in (63, 64, 127, 128, 191, 192)}))
+
+
 @pytest.mark.parametrize("M", [257, 300, 520])
 def test_bf16_wide_tiles(M):
     """256 x 256 tiles (two column groups per work group), taken above 256
@@ -155,6 +163,15 @@ def test_swiglu_split_tail(M, F, K):
     from paper_2609_36899_amd import _native as N
     assert N.load().swiglu_projection_workspace_bytes(N.BF16, M, F, K) > 0
     _swiglu_run(M, F, K, seed=M + F + 1)
+
+
+@pytest.mark.parametrize("M,F,K", [(m, 8256, 320) for m in (48, 63, 64, 65, 191, 192, 193, 320, 449)] +
+                         [(64, 16320, 64), (192, 17408, 320), (300, 17408, 320), (600, 1408, 512)])
+def test_swiglu_row_tiles(M, F, K):
+    """Edges of the 64- to 256-row tiles with the SwiGLU epilogue; 300 rows of
+    F = 17408 take 128-column tiles instead of 272 wide ones, 600 rows of a
+    small FFN may split K."""
+    _swiglu_run(M, F, K, seed=M + F, rows=sorted({0, 31, M // 2, M - 2, M - 1}))
 
 
 @pytest.mark.parametrize("M", [16, 128, 256])
