@@ -440,47 +440,58 @@ __global__ __launch_bounds__(8 * ROWS / MT) void gemm_bf16_tile(int M, int N, in
 }
 
 // Batches above 256 rows (prefill chunks, B = 512 decode): 256 x 256 output
-// tiles, 8 waves in a 4 x 2 grid of 64 x 128 sub-tiles (each wave's columns
-// are one packed group, NT = 8 strips).  Against the 256 x 128 tile this
-// halves the A bytes each output needs from L2 (the A tile is shared by two
-// column groups) and reads 12 fragments from LDS per 32 MFMAs instead of 16.
-// Stages hold one k-block (32): A 256 rows x 64 B (16-byte chunks swizzled
-// by row so that the 16 rows of a fragment read hit distinct banks) and W
-// 2 groups x 8 strips (two contiguous 8 KiB runs); a ring of four stages
-// keeps three k-blocks in flight.  Column tile v covers groups 2v and 2v + 1
-// (the second clamped to a valid group and its outputs dropped when the
-// group count is odd); GLU: column tile v is group v of both matrices, wave
-// column wn taking half wn of it with its strips staged as gate, up, gate,
-// up, ... (four (gate, up) pairs per wave), and the epilogue writes
+// tiles, four waves in a 2 x 2 grid of 128 x 128 sub-tiles (a wave's columns are
+// one packed group, NT = 8 strips).  A large grid of these runs at the card's
+// power limit (1.6-1.8 GHz here), so what a multiply moves counts as well as what
+// it waits for.  A wave of 128 x 128 reads 16 KiB of fragments from LDS for 64
+// MFMAs, a third less than two of 64 x 128; an A stage holds k-blocks in pairs, so
+// that its loads take whole 128-byte lines (64-byte rows made half as many requests
+// to L2 again); v_mfma_f32_32x32x16 took fewer cycles but 8% more time, at a lower
+// clock.  One wave per SIMD has no other wave to cover its LDS reads, so it reads
+// the fragments of the next k-block while this one's multiply (256 accumulator
+// registers and two sets of 64 fragment registers; buffer addressing leaves room
+// for them), a read per three MFMAs and, in the second half of a stage, a load per
+// three: all 16 loads in half the time stall at the 64 bytes a cycle that the
+// texture path takes (5% slower).
+// 4096 rows, us, against eight waves of 64 x 128 and k-blocks staged singly: o of
+// the 8B shape 102 / 117, down 335 / 372 (1.43 PFLOP/s), gate/up 721 / 770.
+// Stages hold two k-blocks of 32: A 256 rows x 128 B and W 2 groups x 2 blocks x 8
+// strips (two contiguous 16 KiB runs), in a ring of two.  Column tile v covers
+// groups 2v and 2v + 1 (the second clamped to a valid group and its outputs
+// dropped when the group count is odd); GLU: column tile v is group v of both
+// matrices, wave column wn taking half wn of it with its strips staged as gate,
+// up, gate, up, ... (four (gate, up) pairs per wave), and the epilogue writes
 // silu(gate) * up as bf16.
+// Work group ids L and L + 8 share an XCD, whose 32 CUs run bands of up to
+// kBandRows M-blocks by four columns of tiles: the 12 tile edges of such a square
+// come through its L2 instead of the 18 of 16 M-blocks by two columns (what down
+// at 4096 rows reads past L2: 389 MB against 516).  K >= 128, a multiple of 64.
+constexpr int kBandRows = 8;
 template <bool GLU>
-__global__ __launch_bounds__(512) void gemm_bf16_wide(int M, int N, int K, int k_split,
-                                                     int n_mb, int n_nb, int n_groups,
-                                                     const uint16_t* __restrict__ A,
-                                                     int64_t lda, WSegs w,
-                                                     float* __restrict__ out,
-                                                     uint16_t* __restrict__ glu_out) {
-  constexpr int MT = 4, NT = 8, D = 4, THREADS = 512, ROWS = 256;
-  constexpr int ACH = ROWS * 4 / THREADS;  // A chunks per thread per stage (2)
-  constexpr int WCH = 1024 / THREADS;      // W chunks per thread per stage (2)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_bf16_wide(
+    int M, int N, int K, int n_mb, int n_nb, int row_x, int n_groups, const uint16_t* __restrict__ A,
+    int64_t lda, WSegs w, float* __restrict__ out, uint16_t* __restrict__ glu_out) {
+  constexpr int MT = 8, NT = 8, THREADS = 256, ROWS = 256;
+  constexpr int ACH = ROWS * 8 / THREADS;  // A chunks per thread per stage (8)
+  constexpr int WCH = 2048 / THREADS;      // W chunks per thread per stage (8)
   constexpr int LPS = ACH + WCH;
-  constexpr int SA = ROWS * 32, STAGE = SA + 2 * 8 * 512;  // elements
+  constexpr int SA = ROWS * 64, STAGE = SA + 2 * 2 * 8 * 512;  // elements
   __shared__ __attribute__((aligned(16))) uint16_t lds0[STAGE];
   __shared__ __attribute__((aligned(16))) uint16_t lds1[STAGE];
-  __shared__ __attribute__((aligned(16))) uint16_t lds2[STAGE];
-  __shared__ __attribute__((aligned(16))) uint16_t lds3[STAGE];
-  auto stage_ptr = [&](int b) -> uint16_t* {
-    return b == 0 ? lds0 : b == 1 ? lds1 : b == 2 ? lds2 : lds3;
-  };
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  auto stage_ptr = [&](int b) -> uint16_t* { return b == 0 ? lds0 : lds1; };
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar, as all it leads to
   const int c16 = lane & 15, q4 = lane >> 4;
-  const int L = blockIdx.x;
-  const int grp = L / (8 * n_mb), rem = L % (8 * n_mb);
-  const int mb = rem / 8, nb = grp * 8 + rem % 8;
+  // XCD x takes columns c, c + cols_x, .. and one of row_x equal parts of the
+  // M-blocks; seq numbers its tiles: bands of M-blocks, a band's columns in turn.
+  const int x = blockIdx.x % 8, seq = blockIdx.x / 8, cols_x = 8 / row_x;
+  const int part = n_mb / row_x, nb_x = (n_nb + cols_x - 1) / cols_x;
+  const int band = seq / (kBandRows * nb_x), in_band = seq % (kBandRows * nb_x);
+  const int band_h = min(kBandRows, part - band * kBandRows);
+  const int mb = x / cols_x * part + band * kBandRows + in_band % band_h;
+  const int nb = in_band / band_h * cols_x + x % cols_x;
   if (nb >= n_nb) return;  // padding of the id layout; uniform over the group
-  const int kbeg = blockIdx.z * k_split;
-  const int n_iter = (min(K, kbeg + k_split) - kbeg) / 32;
-  if (n_iter <= 0) return;
+  const int n_stages = K / 64;
   const int m_blk = mb * ROWS;
   const int wm = wave >> 1, wn = wave & 1;
 
@@ -497,37 +508,37 @@ __global__ __launch_bounds__(512) void gemm_bf16_wide(int M, int N, int K, int k
     col_end = gw < n_groups ? gr.col_end : 0;  // a clamped second group writes nothing
   }
 
-  // A: chunk id = row * 4 + slot, holding source chunk slot ^ ((row >> 1) & 3).
-  // A row is 64 bytes, so two rows share one 128-byte span of the banks; a
-  // fragment read (eight consecutive lanes = eight consecutive rows, one
-  // logical chunk) then lands on eight distinct 16-byte bank groups: even and
-  // odd rows take the two halves, and (row >> 1) & 3 spreads the four of each.
-  const uint16_t* asrc[ACH];
+  // A: chunk id = row * 8 + slot, holding source chunk slot ^ (row & 7).
+  // Load j takes rows 32 j .. 32 j + 31; rows past M lie outside the buffer.
+  const Buffer abuf = make_buffer(A + (int64_t)m_blk * lda,
+                                  (uint32_t)min(ROWS, M - m_blk) * (uint32_t)(lda * 2));
+  const int aofs = (tid >> 3) * (int)(lda * 2) + (((tid & 7) ^ ((tid >> 3) & 7)) * 16);
+  const int arow32 = 32 * (int)(lda * 2);
+  // W: chunk id = ((g2 * 2 + kb) * 8 + sp) * 64 + lane of staged group g2 (the
+  // wave column that reads it), k-block kb, staged strip sp.  Load j brings strip
+  // sp = 4 (j % 2) + wave of k-block (j / 2) % 2 and group j / 4; GLU: strip
+  // 4 g2 + sp / 2 of gate (sp even) or up, for a wave always the same matrix.
+  Buffer wbuf[2];
+  int wofs;  // of the lane in the strips of load 0
+  if constexpr (GLU) {
+    wbuf[0] = wbuf[1] = make_buffer(
+        (const uint16_t*)w.ptr[wave & 1] + (int64_t)nb * kGroupCols * K, (uint32_t)K * 256u);
+    wofs = (wave >> 1) * 1024 + lane * 16;
+  } else {
 #pragma unroll
-  for (int j = 0; j < ACH; ++j) {
-    const int id = j * THREADS + tid, r = id >> 2, slot = id & 3;
-    asrc[j] = A + (int64_t)min(m_blk + r, M - 1) * lda + kbeg + ((slot ^ ((r >> 1) & 3)) * 8);
+    for (int g2 = 0; g2 < 2; ++g2)
+      wbuf[g2] = make_buffer(group_ref(w, min(2 * nb + g2, n_groups - 1), K).base,
+                             (uint32_t)K * 256u);
+    wofs = wave * 1024 + lane * 16;
   }
-  // W: chunk id = (g2 * 8 + sp) * 64 + lane of staged group g2 (the wave
-  // column that reads it), staged strip sp.
-  const uint16_t* wsrc[WCH];
+  // Fragments of k-block h of a stage.  Rows are 128 bytes: the eight consecutive
+  // lanes of a read are eight rows and one logical chunk, swizzled to eight
+  // distinct 16-byte bank groups.
+  int aoff[2];  // row tile t: + t * 1024 elements (16 rows; the swizzle repeats every 8)
 #pragma unroll
-  for (int j = 0; j < WCH; ++j) {
-    const int id = j * THREADS + tid, g2 = id >> 9, sp = (id >> 6) & 7, ln = id & 63;
-    if constexpr (GLU) {
-      wsrc[j] = (const uint16_t*)w.ptr[sp & 1] + (int64_t)nb * kGroupCols * K +
-                ((int64_t)(kbeg / 32) * 8 + 4 * g2 + (sp >> 1)) * 512 + ln * 8;
-    } else {
-      const GroupRef gs = group_ref(w, min(2 * nb + g2, n_groups - 1), K);
-      wsrc[j] = gs.base + ((int64_t)(kbeg / 32) * 8 + sp) * 512 + ln * 8;
-    }
-  }
-  int aoff[MT];
-#pragma unroll
-  for (int t = 0; t < MT; ++t) {
-    const int ra = wm * 64 + t * 16 + c16;
-    aoff[t] = ra * 32 + ((q4 ^ ((ra >> 1) & 3)) * 8);
-  }
+  for (int h = 0; h < 2; ++h)
+    aoff[h] = (wm * 128 + c16) * 64 + (((4 * h + q4) ^ (c16 & 7)) * 8);
+  const int woff = SA + wn * 16 * 512 + lane * 8;
 
   f32x4 acc[MT][NT];
 #pragma unroll
@@ -535,56 +546,84 @@ __global__ __launch_bounds__(512) void gemm_bf16_wide(int M, int N, int K, int k
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  auto issue = [&](int i, int b) {
+  auto issue1 = [&](int i, int b, int j) {  // load j of stage i into slot b
     uint16_t* base = stage_ptr(b) + wave * 64 * 8;
-#pragma unroll
-    for (int j = 0; j < ACH; ++j) dma16(asrc[j] + i * 32, base + j * THREADS * 8);
-#pragma unroll
-    for (int j = 0; j < WCH; ++j)
-      dma16_stream(wsrc[j] + (int64_t)i * 4096, base + SA + j * THREADS * 8);
-  };
-  auto compute = [&](int b) {
-    const uint16_t* la = stage_ptr(b);
-    const uint16_t* lw = la + SA + wn * 8 * 512;
-    bf16x8 af[MT], bf[NT];
-#pragma unroll
-    for (int t = 0; t < MT; ++t) af[t] = *(const bf16x8*)(la + aoff[t]);
-#pragma unroll
-    for (int t = 0; t < NT; ++t) bf[t] = *(const bf16x8*)(lw + (t * 64 + lane) * 8);
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-      for (int j = 0; j < NT; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
-  };
-  // As in the 256 x 128 tile: every step issues one stage (the prefetch index
-  // clamped to the last step), so waiting until D - 2 stages are outstanding
-  // means this wave's part of step it has landed; the barrier covers the
-  // other waves' parts and frees the stage that step it + D - 1 refills.
-  const int last = n_iter - 1;
-#pragma unroll
-  for (int s = 0; s < D - 1; ++s) issue(min(s, last), s);
-  int it = 0;
-  for (; it + D <= n_iter; it += D) {
-#pragma unroll
-    for (int s = 0; s < D; ++s) {
-      wait_vmem<(D - 2) * LPS>();
-      wg_barrier();
-      issue(min(it + s + D - 1, last), (s + D - 1) % D);
-      __builtin_amdgcn_sched_barrier(0);
-      compute(s);
+    if (j < ACH) {
+      dma16_buf<false>(abuf, aofs, i * 128 + j * arow32, base + j * THREADS * 8);
+    } else {
+      const int jw = j - ACH, kb = (jw >> 1) & 1, hi = jw & 1, g2 = jw >> 2;
+      const int strip = GLU ? kb * 8 + 4 * g2 + 2 * hi : kb * 8 + 4 * hi;
+      dma16_buf<true>(wbuf[g2], wofs, i * 16384 + strip * 1024, base + SA + jw * THREADS * 8);
     }
+  };
+  // Fragment r of the 16 of a k-block in order of use: the first A row tile, the W
+  // strips, the other row tiles.
+  bf16x8 fa[2][MT], fb[2][NT];
+  auto read1 = [&](int b, int h, int r) {
+    const uint16_t* p = stage_ptr(b);
+    if (r == 0)
+      fa[h][0] = *(const bf16x8*)(p + aoff[h]);
+    else if (r <= NT)
+      fb[h][r - 1] = *(const bf16x8*)(p + woff + h * 4096 + (r - 1) * 512);
+    else
+      fa[h][r - NT] = *(const bf16x8*)(p + aoff[h] + (r - NT) * 1024);
+  };
+  auto mma1 = [&](int h, int x) {
+    const int i = x / NT, j = x % NT;
+    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[h][i], fb[h][j], acc[i][j], 0, 0, 0);
+  };
+  // Stage st, in slot b, its first k-block's fragments already in registers.  First
+  // half: multiply them and read the second k-block's.  Then this wave is done with
+  // the slot and, with its loads in flight at zero, its part of stage st + 1 has
+  // landed; behind the barrier that holds for all waves.  Second half: multiply,
+  // read the first fragments of stage st + 1 and refill the slot with stage st + 2
+  // (both clamped to the last stage: what the clamped ones bring is not used).
+  const int last = n_stages - 1;
+  auto stage = [&](int st, int b) {
+#pragma unroll
+    for (int x = 0; x < MT * NT; ++x) {
+      mma1(0, x);
+      if (x % 3 == 0 && x / 3 < MT + NT) read1(b, 1, x / 3);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    wait_vmem<0>();
+    wg_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    const int pre = min(st + 2, last);
+#pragma unroll
+    for (int x = 0; x < MT * NT; ++x) {
+      mma1(1, x);
+      if (x % 3 == 0 && x / 3 < LPS) issue1(pre, b, x / 3);
+      if (x % 3 == 1 && x / 3 < MT + NT) read1(b ^ 1, 0, x / 3);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto fill = [&](int b) {  // stage 0 into slot b, stage 1 into the other; the first fragments
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int j = 0; j < LPS; ++j) issue1(s, b ^ s, j);
+    wait_vmem<LPS>();
+    wg_barrier();
+#pragma unroll
+    for (int r = 0; r < MT + NT; ++r) read1(b, 0, r);
+  };
+  // An odd number of stages runs the first ahead of the loop in slot 1, which leaves
+  // the loop whole turns of the ring and one exit (with a tail behind it the
+  // compiler moves accumulators between registers on every turn).
+  int st = n_stages & 1;
+  if (st) {
+    fill(1);
+    stage(0, 1);
+  } else {
+    fill(0);
   }
-  const int tail = n_iter - it;  // uniform over the work group
-#pragma unroll
-  for (int s = 0; s < D; ++s)
-    if (s < tail) {
-      wait_vmem<(D - 2) * LPS>();
-      wg_barrier();
-      issue(min(it + s + D - 1, last), (s + D - 1) % D);
-      __builtin_amdgcn_sched_barrier(0);
-      compute(s);
-    }
+  do {
+    stage(st, 0);
+    stage(st + 1, 1);
+    st += 2;
+  } while (st < n_stages);
   wait_vmem<0>();  // no LDS write may still be in flight when the group ends
 
   if constexpr (GLU) {
@@ -595,14 +634,13 @@ __global__ __launch_bounds__(512) void gemm_bf16_wide(int M, int N, int K, int k
         const int col = col0 + p * 16 + c16;
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) {
-          const int row = m_blk + wm * 64 + i * 16 + 4 * q4 + rr;
+          const int row = m_blk + wm * 128 + i * 16 + 4 * q4 + rr;
           if (row < M && col < col_end)
             glu_out[(int64_t)row * N + col] =
                 f32_to_bf16(silu_mul(acc[i][2 * p][rr], acc[i][2 * p + 1][rr]));
         }
       }
   } else {
-    float* o = out + (int64_t)blockIdx.z * M * N;
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -610,8 +648,8 @@ __global__ __launch_bounds__(512) void gemm_bf16_wide(int M, int N, int K, int k
         const int col = col0 + j * 16 + c16;
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) {
-          const int row = m_blk + wm * 64 + i * 16 + 4 * q4 + rr;
-          if (row < M && col < col_end) o[(int64_t)row * N + col] = acc[i][j][rr];
+          const int row = m_blk + wm * 128 + i * 16 + 4 * q4 + rr;
+          if (row < M && col < col_end) out[(int64_t)row * N + col] = acc[i][j][rr];
         }
       }
   }
@@ -767,11 +805,14 @@ constexpr int kStreamMaxRows = 32;
 // rounds of 192 instead of one and an eighth of 256), 44.6 / 52.1 at 600 (128-row
 // tiles), down 174 / 191 at 1400 and 60.7 / 68.3 at 300.
 //
-// The 256 x 256 tile enters the same comparison, unsplit and at 111 us a round,
-// where its grid alone nearly fills the GPU (gate/up and the LM head at any M >
-// 256): where it would need more K splits than the 256 x 128 tile (o, down, qkv at
-// 384-1024 rows) the extra partial traffic made it 5-45% slower.  Gate/up of the
-// 14B shape at 300 rows, 272 wide tiles, is one it loses: 273 us against 183.
+// The 256 x 256 tile enters the same comparison, unsplit and at 102 us a round (o of
+// the 8B shape at 4096 rows, one round: 102 us; 115 on eight waves of 64 x 128), from
+// two k-steps of 64 on, which its ring of stages needs.  Taken where that is
+// estimated less: gate/up and the LM head at most row counts, qkv of the 8B shape
+// at 2048 rows (192 tiles, 98 us against 125 on 128-column tiles) and 4096 (194 /
+// 215), down of the 14B shape at 2048 (350 / 443).  Left where it would leave most
+// CUs idle (o, down, qkv below about 1200 rows) and at gate/up of the 14B shape
+// with 300 rows, 272 wide tiles: 183 us on 128-column tiles, 273 on wide ones.
 struct TilePlan {
   int rows, splits;  // rows of the 128-column tile
   bool wide;         // the 256 x 256 tile instead (splits = 1)
@@ -795,8 +836,8 @@ TilePlan plan_tile(int M, int K, int64_t groups, bool glu, bool may_widen) {
   TilePlan best{256, 1, false};
   double least = 1e30;
   const int64_t wide = (groups + 1) / 2 * ((m + 255) / 256);
-  if (may_widen && wide >= 224) {
-    least = grid_rounds(wide) * 111 * K / 4096;
+  if (may_widen && K >= 128) {
+    least = grid_rounds(wide) * 102 * K / 4096;
     best.wide = true;
   }
   for (int rows = 256; rows >= 128; rows -= 64) {
@@ -884,14 +925,17 @@ hipError_t launch_gemm_bf16(int M, int N, int K, const uint16_t* a, int64_t lda,
     return launch_timed(gemm_bf16_stream<2, 2, GLU>, grid, dim3(256), stream, ev_start, ev_stop,
                         M, N, K, k_split, a, lda, w, out, glu_out);
   }
-  // Plain matrices given as several segments (q|k|v) keep the 128-column tile.
-  const TilePlan plan = plan_tile(M, K, n_groups, GLU, splits == 1 && (GLU || w.n_seg == 1));
+  const TilePlan plan = plan_tile(M, K, n_groups, GLU, splits == 1);
   if (plan.wide) {
     // GLU: n_groups counts half-groups; a wide column tile is one whole group.
     const int n_mb = (M + 255) / 256, n_nb = GLU ? n_groups / 2 : (n_groups + 1) / 2;
-    const dim3 grid(((n_nb + 7) / 8) * 8 * n_mb, 1, splits);
-    return launch_timed(gemm_bf16_wide<GLU>, grid, dim3(512), stream, ev_start, ev_stop, M, N, K,
-                        k_split, n_mb, n_nb, n_groups, a, lda, w, out, glu_out);
+    // Columns by XCD alone would give each fewer than four: two halves of the
+    // M-blocks keep its share of the grid near square.
+    const int row_x = n_mb >= 2 * kBandRows && n_mb % 2 == 0 && n_nb < 32 ? 2 : 1;
+    const int cols_x = 8 / row_x;
+    const dim3 grid(8 * ((n_nb + cols_x - 1) / cols_x) * (n_mb / row_x));
+    return launch_timed(gemm_bf16_wide<GLU>, grid, dim3(256), stream, ev_start, ev_stop, M, N, K,
+                        n_mb, n_nb, row_x, n_groups, a, lda, w, out, glu_out);
   }
   const int rows = plan.rows;
   const int n_mb = (M + rows - 1) / rows, n_nb = n_groups;

@@ -43,6 +43,19 @@ __device__ __forceinline__ void dma16_stream(const void* src, void* lds) {
                                    (__attribute__((address_space(3))) void*)lds, 16, 0, 2);
 }
 
+// The same from a buffer (a wave-uniform base and size; what lies outside is not
+// read): byte offset voff of the lane plus the uniform soff.  It needs one offset
+// register where global addresses take two and a 64-bit add per load.
+typedef __amdgpu_buffer_rsrc_t Buffer;
+__device__ __forceinline__ Buffer make_buffer(const void* base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000);
+}
+template <bool STREAM>
+__device__ __forceinline__ void dma16_buf(Buffer src, int voff, int soff, void* lds) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void*)lds, 16,
+                                           voff, soff, 0, STREAM ? 2 : 0);
+}
+
 // Wait until at most N vector-memory operations of this wave are outstanding
 // (loads retire in issue order), leaving the other counters alone.
 template <int N>

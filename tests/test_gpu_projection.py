@@ -79,6 +79,23 @@ def test_bf16_wide_tiles(M):
     _run(M, 28736, 320, seed=M, rows=rows)
 
 
+@pytest.mark.parametrize("M,N,K", [
+    (4096, 4096, 192), (4609, 3000, 128),  # M-blocks in halves (16 and, with one more, none)
+    (4600, 3000, 320), (2100, 6000, 64),   # 18 M-blocks; one k-step is too few for the ring
+    (1300, 6144, 576)])
+def test_bf16_wide_tile_grids(M, N, K):
+    """Grids of 256 x 256 tiles: bands and halves of M-blocks per XCD, odd and even
+    numbers of 64-deep stages, odd numbers of column groups, ragged last rows."""
+    rows = sorted({0, 127, 128, 255, 256, 2047, 2048, M - 257, M - 1} - set(range(M, 5000)))
+    _run(M, N, K, seed=M + K, rows=rows)
+
+
+@pytest.mark.parametrize("M,F,K", [(2100, 8256, 192), (4096, 1088, 128), (520, 16320, 448)])
+def test_swiglu_wide_tile_grids(M, F, K):
+    """The same with the SwiGLU epilogue; F ends in a half-filled group."""
+    _swiglu_run(M, F, K, seed=M + F, rows=sorted({0, 127, 255, 256, M // 2, M - 257, M - 1}))
+
+
 @pytest.mark.parametrize("M", [1, 4, 33])
 def test_f32(M):
     _run(M, 688, 256, bf16=False, seed=M)
