@@ -495,6 +495,15 @@ int paged_decode_attention_fp8(int32_t batch, int32_t n_q_heads, int32_t n_kv_he
                                const int32_t* lens_host, float* out, void* workspace,
                                int64_t workspace_bytes, void* stream);
 
+/* Which rows of a device block table name pages outside [0, n_pages) among the
+ * (lens[b] + 15) / 16 entries the attention reads.  Writes
+ * PDEC_CHECK_WORDS(batch) words to device memory, in stream order: the lowest
+ * bad row is their minimum, INT32_MAX where there is none.  lens is read on
+ * the host, before the call returns. */
+#define PDEC_CHECK_WORDS(batch) (((batch) + 127) / 128 * 32)
+int paged_check_pages(int32_t batch, const int32_t* block_table, int32_t bt_stride,
+                      const int32_t* lens, int64_t n_pages, int32_t* words, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -104,6 +104,8 @@ SIGNATURES = {
     "paged_decode_attention": (c_int32, [c_int32, c_int32, c_int32, c_int32, c_int32, c_void_p,
                                          c_void_p, c_void_p, c_void_p, c_int32, POINTER(c_int32),
                                          c_void_p, c_void_p, c_int64, c_void_p]),
+    "paged_check_pages": (c_int32, [c_int32, c_void_p, c_int32, POINTER(c_int32), c_int64,
+                                    c_void_p, c_void_p]),
     "paged_decode_attention_fp8": (c_int32, [c_int32, c_int32, c_int32, c_int32, c_void_p, c_void_p,
                                              c_void_p, c_float, c_float, c_void_p, c_int32,
                                              POINTER(c_int32), c_void_p, c_void_p, c_int64,

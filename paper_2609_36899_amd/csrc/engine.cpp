@@ -1321,4 +1321,23 @@ int paged_decode_attention_fp8(int32_t B, int32_t Hq, int32_t Hkv, int32_t Dh, c
                               v_pages, bt, bt_stride, lens, out, workspace, ws_bytes, stream);
 }
 
+int paged_check_pages(int32_t B, const int32_t* bt, int32_t bt_stride, const int32_t* lens,
+                      int64_t n_pages, int32_t* words, void* stream) {
+  static_assert(PDEC_CHECK_WORDS(1) == kCheckGroups && PDEC_CHECK_WORDS(kCheckRows + 1) == 2 * kCheckGroups,
+                "the header's word count");
+  if (!bt || !lens || !words) return fail(PDEC_INVALID_ARG, "null argument");
+  if (B < 1 || bt_stride < 1) return fail(PDEC_INVALID_ARG, "bad sizes");
+  for (int b = 0; b < B; ++b)
+    if (lens[b] < 1 || (int64_t)lens[b] > (int64_t)bt_stride * kPage)
+      return fail(PDEC_INVALID_ARG, "lens[b] outside [1, bt_stride*16]");
+  for (int b0 = 0; b0 < B; b0 += kCheckRows) {
+    CheckRows rows{};
+    const int n = std::min(kCheckRows, B - b0);
+    for (int b = 0; b < n; ++b) rows.pages[b] = PagePool::pages_for(lens[b0 + b]);
+    HIP_OR_FAIL(launch_check_pages(b0, n, rows, bt, bt_stride, n_pages,
+                                   words + b0 / kCheckRows * kCheckGroups, (hipStream_t)stream));
+  }
+  return PDEC_OK;
+}
+
 }  // extern "C"

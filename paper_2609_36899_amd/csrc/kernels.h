@@ -159,6 +159,15 @@ hipError_t launch_argmax(int B, int V, const float* logits, int32_t* tokens, voi
 // bt[d.slot * stride + d.idx] = d.page for each delta.
 hipError_t launch_bt_deltas(int n, const BtDelta* deltas, int32_t* bt, int32_t stride,
                             hipStream_t stream);
+// words[k] = the lowest of rows [row0, row0 + n) whose first pages[row - row0]
+// entries hold an id outside [0, n_pages), of those work group k looked at;
+// INT32_MAX if none (kCheckGroups words).
+constexpr int kCheckRows = 128, kCheckGroups = 32;
+struct CheckRows {
+  int32_t pages[kCheckRows];
+};
+hipError_t launch_check_pages(int row0, int n, const CheckRows& rows, const int32_t* bt,
+                              int32_t stride, int64_t n_pages, int32_t* words, hipStream_t stream);
 // cs[p][i] = (cos, sin)(p * base^(-2i/Dh)) evaluated in double precision.
 hipError_t launch_rope_table(int max_pos, int head_dim, double base, float2* cs,
                              hipStream_t stream);

@@ -462,6 +462,29 @@ inline int grid_for(int64_t n, int block) {
   return (int)std::min<int64_t>((n + block - 1) / block, 65536);
 }
 
+// A table's page ids against the pool: groups split the rows, or each row when
+// there are few.  65K entries take about 4 us, where copying the table to the host
+// and scanning it there held an attention call back by 45.
+__global__ __launch_bounds__(256) void check_pages_kernel(int row0, int n, CheckRows rows,
+                                                          const int32_t* __restrict__ bt,
+                                                          int32_t stride, int64_t n_pages,
+                                                          int32_t* __restrict__ words) {
+  __shared__ int32_t worst;
+  if (threadIdx.x == 0) worst = INT32_MAX;
+  __syncthreads();
+  const int parts = max(1, kCheckGroups / n);  // work groups per row
+  const int part = blockIdx.x % parts, step = kCheckGroups / parts;
+  for (int r = blockIdx.x / parts; r < n; r += step) {
+    const int32_t* row = bt + (int64_t)(row0 + r) * stride;
+    bool bad = false;
+    for (int i = part * 256 + threadIdx.x; i < rows.pages[r]; i += parts * 256)
+      bad |= row[i] < 0 || row[i] >= n_pages;
+    if (bad) atomicMin(&worst, row0 + r);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) words[blockIdx.x] = worst;
+}
+
 }  // namespace
 
 hipError_t launch_embed_norm(int dtype, int M, int d, int vocab, const int32_t* tokens,
@@ -580,6 +603,14 @@ hipError_t launch_bt_deltas(int n, const BtDelta* deltas, int32_t* bt, int32_t s
                             hipStream_t stream) {
   if (n == 0) return hipSuccess;
   bt_deltas_kernel<<<(n + 255) / 256, 256, 0, stream>>>(n, deltas, bt, stride);
+  return hipGetLastError();
+}
+
+hipError_t launch_check_pages(int row0, int n, const CheckRows& rows, const int32_t* bt,
+                              int32_t stride, int64_t n_pages, int32_t* words,
+                              hipStream_t stream) {
+  if (n <= 0) return hipSuccess;
+  check_pages_kernel<<<kCheckGroups, 256, 0, stream>>>(row0, n, rows, bt, stride, n_pages, words);
   return hipGetLastError();
 }
 

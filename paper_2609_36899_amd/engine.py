@@ -376,6 +376,32 @@ def paged_attention_workspace_bytes(batch: int, n_q_heads: int, n_kv_heads: int,
                                                             head_dim, 0))
 
 
+def _check_pages(block_table: torch.Tensor, lens: np.ndarray, n_pages: int) -> None:
+    """Refuse a block table whose used entries leave the pool.  The GPU looks and a few
+    words are copied to the host, except for a small table of up to three rows, which
+    is copied itself (2 rows of 300 tokens: 41 us a call against 49; 8 rows of 100,000
+    tokens 356 against 311, 128 of 2000 346 against 129)."""
+    rows = block_table.shape[0]
+    bad = rows
+    if block_table.is_cuda and (rows > 3 or block_table.numel() > 8192):
+        words = torch.empty((rows + 127) // 128 * 32, dtype=torch.int32,
+                            device=block_table.device)
+        N.check(N.load().paged_check_pages(
+            rows, block_table.data_ptr(), block_table.shape[1],
+            lens.ctypes.data_as(POINTER(c_int32)), n_pages, words.data_ptr(),
+            _stream_handle(None)))
+        bad = int(words.cpu().numpy().min())
+    else:
+        bt = block_table.cpu().numpy()
+        for b in range(rows):
+            used = bt[b, :(int(lens[b]) + PAGE_TOKENS - 1) // PAGE_TOKENS]
+            if used.size and (used.min() < 0 or used.max() >= n_pages):
+                bad = b
+                break
+    if bad < rows:
+        raise PdecError(N.INVALID_ARG, f"block table row {bad} names a page outside the pool")
+
+
 def paged_decode_attention_fp8(q: torch.Tensor, k_pages: torch.Tensor, v_pages: torch.Tensor,
                                k_scale: float, v_scale: float, block_table: torch.Tensor,
                                lens: Sequence[int], out: torch.Tensor,
@@ -393,11 +419,7 @@ def paged_decode_attention_fp8(q: torch.Tensor, k_pages: torch.Tensor, v_pages: 
     assert out.dtype == torch.float32 and tuple(out.shape) == (B, Hq, Dh) and out.is_contiguous()
     ln = np.ascontiguousarray(np.asarray(lens, dtype=np.int32))
     assert ln.shape == (B,) and (ln >= 1).all() and (ln <= block_table.shape[1] * PAGE_TOKENS).all()
-    bt = block_table.cpu().numpy()
-    for b in range(B):
-        used = bt[b, :(int(ln[b]) + PAGE_TOKENS - 1) // PAGE_TOKENS]
-        if used.size and (used.min() < 0 or used.max() >= P):
-            raise PdecError(N.INVALID_ARG, f"block table row {b} names a page outside the pool")
+    _check_pages(block_table, ln, P)
     need = paged_attention_workspace_bytes(B, Hq, Hkv, Dh)
     if workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
@@ -435,11 +457,7 @@ def paged_decode_attention(q: torch.Tensor, k_pages: torch.Tensor, v_pages: torc
     ln = np.ascontiguousarray(np.asarray(lens, dtype=np.int32))
     assert ln.shape == (B,) and (ln >= 1).all() and (ln <= block_table.shape[1] * PAGE_TOKENS).all()
     if check_pages:
-        bt = block_table.cpu().numpy()
-        for b in range(B):
-            used = bt[b, :(int(ln[b]) + PAGE_TOKENS - 1) // PAGE_TOKENS]
-            if used.size and (used.min() < 0 or used.max() >= P):
-                raise PdecError(N.INVALID_ARG, f"block table row {b} names a page outside the pool")
+        _check_pages(block_table, ln, P)
     need = paged_attention_workspace_bytes(B, Hq, Hkv, Dh)
     if workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=q.device)

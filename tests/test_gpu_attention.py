@@ -222,3 +222,25 @@ def test_bf16_full_size_b8_long_sampled():
     lens = lengths_uniform(8, 65536, 131072, 1)
     sampled = sorted({int(np.argmax(lens)), 0, 5})
     _full_size_sampled(lens, sampled, seed=32)
+
+
+@pytest.mark.parametrize("B,stride,n", [(2, 1, 16), (5, 300, 4800), (32, 9, 144), (33, 3, 40),
+                                        (129, 2, 17), (300, 1, 1)])
+def test_check_pages_names_the_first_bad_row(B, stride, n):
+    """Ids outside the pool are refused in any used entry, at the first and last row
+    of a launch of 128 and with rows split over work groups; unused entries and the
+    largest id pass."""
+    from paper_2609_36899_amd.engine import _check_pages
+    P = _pdec()
+    lens = np.full(B, n, dtype=np.int32)
+    used = (n + 15) // 16
+    good = np.full((B, stride), 6, dtype=np.int32)
+    good[:, used:] = 99
+    _check_pages(torch.from_numpy(good).cuda(), lens, 7)
+    for row, col, bad in [(0, 0, 7), (B - 1, used - 1, -1), (B // 2, used // 2, 1 << 30),
+                          (min(B - 1, 128), 0, 7)]:
+        t = good.copy()
+        t[row, col] = bad
+        t[B - 1, 0] = 7  # a later bad row
+        with pytest.raises(P.PdecError, match=f"row {row} "):
+            _check_pages(torch.from_numpy(t).cuda(), lens, 7)
