@@ -352,15 +352,27 @@ __global__ __launch_bounds__(8 * ROWS / MT) void gemm_bf16_tile(int M, int N, in
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  auto issue = [&](int i, int b) {
+  auto issue1 = [&](int i, int b, int j) {  // load j of step i into stage b, W first
     uint16_t* base = stage_ptr(b) + wave * 64 * 8;
-#pragma unroll
-    for (int j = 0; j < ACH; ++j) dma16(asrc[j] + i * 64, base + j * THREADS * 8);
-#pragma unroll
-    for (int j = 0; j < WCH; ++j)
+    if (j < WCH)
       dma16_stream(wsrc[j] + (int64_t)i * 8192, base + SA + j * THREADS * 8);
+    else
+      dma16(asrc[j - WCH] + i * 64, base + (j - WCH) * THREADS * 8);
   };
-  auto compute = [&](int b) {
+  auto issue = [&](int i, int b) {
+#pragma unroll
+    for (int j = 0; j < LPS; ++j) issue1(i, b, j);
+  };
+  // The step in stage b, with the loads of step i_next: one behind each row of MFMAs
+  // where they fit (all at once, eight waves stall on the 64 bytes a cycle of the
+  // texture path: FFN of the 14B shape at 200 rows 1% slower, tool-output append
+  // 0.5%), or all ahead of them (the 64-row tile, which lives on loads in flight).
+  constexpr bool kSpread = 2 * MT >= LPS;
+  auto compute = [&](int b, int i_next, int b_next) {
+    if constexpr (!kSpread) {
+      issue(i_next, b_next);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     const uint16_t* la = stage_ptr(b);
     const uint16_t* lw = la + SA;
 #pragma unroll
@@ -372,10 +384,15 @@ __global__ __launch_bounds__(8 * ROWS / MT) void gemm_bf16_tile(int M, int N, in
       for (int t = 0; t < NT; ++t)
         bf[t] = *(const bf16x8*)(lw + ((h * 8 + wn * 4 + t) * 64 + lane) * 8);
 #pragma unroll
-      for (int i = 0; i < MT; ++i)
+      for (int i = 0; i < MT; ++i) {
 #pragma unroll
         for (int j = 0; j < NT; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
+        if constexpr (kSpread) {
+          if (h * MT + i < LPS) issue1(i_next, b_next, h * MT + i);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
     }
   };
   // Every step issues one stage (the prefetch index clamped to the last
@@ -392,9 +409,7 @@ __global__ __launch_bounds__(8 * ROWS / MT) void gemm_bf16_tile(int M, int N, in
     for (int s = 0; s < D; ++s) {
       wait_vmem<(D - 2) * LPS>();
       wg_barrier();
-      issue(min(it + s + D - 1, last), (s + D - 1) % D);
-      __builtin_amdgcn_sched_barrier(0);
-      compute(s);
+      compute(s, min(it + s + D - 1, last), (s + D - 1) % D);
     }
   }
   const int tail = n_iter - it;  // uniform over the work group
@@ -403,9 +418,7 @@ __global__ __launch_bounds__(8 * ROWS / MT) void gemm_bf16_tile(int M, int N, in
     if (s < tail) {
       wait_vmem<(D - 2) * LPS>();
       wg_barrier();
-      issue(min(it + s + D - 1, last), (s + D - 1) % D);
-      __builtin_amdgcn_sched_barrier(0);
-      compute(s);
+      compute(s, min(it + s + D - 1, last), (s + D - 1) % D);
     }
   wait_vmem<0>();  // no LDS write may still be in flight when the group ends
 
