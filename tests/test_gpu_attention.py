@@ -224,7 +224,7 @@ def test_bf16_full_size_b8_long_sampled():
     _full_size_sampled(lens, sampled, seed=32)
 
 
-@pytest.mark.parametrize("B,stride,n", [(2, 1, 16), (5, 300, 4800), (32, 9, 144), (33, 3, 40),
+@pytest.mark.parametrize("B,stride,n", [(2, 1, 16), (5, 1700, 27200), (32, 9, 144), (33, 3, 40),
                                         (129, 2, 17), (300, 1, 1)])
 def test_check_pages_names_the_first_bad_row(B, stride, n):
     """Ids outside the pool are refused in any used entry, at the first and last row
