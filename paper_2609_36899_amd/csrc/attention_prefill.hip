@@ -285,8 +285,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
   int next_a = page_a_of(min(D - 1, last)), next_b = page_b_of(min(D - 1, last));
   auto step = [&](int s, int b) {
     if constexpr (kFp8) {
-      wait_lds();  // this wave's stage writes of the previous step
-      wg_barrier();
+      wg_barrier();  // with it, the stage writes of the previous step
       load_codes(next_a, next_b);  // stage min(s + D - 1, last)
     } else {
       wait_vmem<(D - 2) * LPT>();

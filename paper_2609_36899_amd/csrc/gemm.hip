@@ -599,7 +599,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       if (x % 3 == 0 && x / 3 < MT + NT) read1(b, 1, x / 3);
       __builtin_amdgcn_sched_barrier(0);
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     wait_vmem<0>();
     wg_barrier();
     __builtin_amdgcn_sched_barrier(0);

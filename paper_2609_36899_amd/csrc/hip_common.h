@@ -71,11 +71,15 @@ __device__ __forceinline__ void wait_lds() {
 }
 
 // Work-group barrier without the fence of __syncthreads, whose release would
-// wait for every load in flight (LDS-DMA loads included).  Callers order
-// their memory with explicit counter waits; the empty asm statements keep
-// the compiler from moving memory accesses across the barrier.
+// wait for every load in flight (LDS-DMA loads included).  Callers wait for
+// loads with wait_vmem; the empty asm statements keep the compiler from moving
+// memory accesses across the barrier.  What a wave has asked of LDS before the
+// barrier is done when it passes: behind it the others refill the stage that it
+// has read, and a read that had only been issued would take the new bytes (the
+// compiler does leave reads in flight here, their MFMAs moved past the barrier).
 __device__ __forceinline__ void wg_barrier() {
   asm volatile("" ::: "memory");
+  wait_lds();
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }
