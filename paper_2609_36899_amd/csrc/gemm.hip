@@ -522,11 +522,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
 
   // A: chunk id = row * 8 + slot, holding source chunk slot ^ (row & 7).
-  // Load j takes rows 32 j .. 32 j + 31; rows past M lie outside the buffer.
+  // Load j takes rows 32 j .. 32 j + 31; rows past M lie outside the buffer.  The
+  // row is part of the lane's offset, which the bounds check counts; the uniform
+  // offset, which the check may leave out, only moves along a row.
   const Buffer abuf = make_buffer(A + (int64_t)m_blk * lda,
                                   (uint32_t)min(ROWS, M - m_blk) * (uint32_t)(lda * 2));
-  const int aofs = (tid >> 3) * (int)(lda * 2) + (((tid & 7) ^ ((tid >> 3) & 7)) * 16);
-  const int arow32 = 32 * (int)(lda * 2);
+  int aofs[ACH];
+#pragma unroll
+  for (int j = 0; j < ACH; ++j)
+    aofs[j] = (32 * j + (tid >> 3)) * (int)(lda * 2) + (((tid & 7) ^ ((tid >> 3) & 7)) * 16);
   // W: chunk id = ((g2 * 2 + kb) * 8 + sp) * 64 + lane of staged group g2 (the
   // wave column that reads it), k-block kb, staged strip sp.  Load j brings strip
   // sp = 4 (j % 2) + wave of k-block (j / 2) % 2 and group j / 4; GLU: strip
@@ -562,7 +566,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   auto issue1 = [&](int i, int b, int j) {  // load j of stage i into slot b
     uint16_t* base = stage_ptr(b) + wave * 64 * 8;
     if (j < ACH) {
-      dma16_buf<false>(abuf, aofs, i * 128 + j * arow32, base + j * THREADS * 8);
+      dma16_buf<false>(abuf, aofs[j], i * 128, base + j * THREADS * 8);
     } else {
       const int jw = j - ACH, kb = (jw >> 1) & 1, hi = jw & 1, g2 = jw >> 2;
       const int strip = GLU ? kb * 8 + 4 * g2 + 2 * hi : kb * 8 + 4 * hi;

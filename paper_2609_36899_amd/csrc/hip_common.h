@@ -43,9 +43,11 @@ __device__ __forceinline__ void dma16_stream(const void* src, void* lds) {
                                    (__attribute__((address_space(3))) void*)lds, 16, 0, 2);
 }
 
-// The same from a buffer (a wave-uniform base and size; what lies outside is not
-// read): byte offset voff of the lane plus the uniform soff.  It needs one offset
-// register where global addresses take two and a 64-bit add per load.
+// The same from a buffer (a wave-uniform base and size): byte offset voff of the
+// lane plus the uniform soff.  It needs one offset register where global addresses
+// take two and a 64-bit add per load.  A lane whose voff lies outside reads nothing.
+// The compiler describes soff as excluded from that check, so callers keep voff +
+// soff inside the buffer wherever voff alone is.
 typedef __amdgpu_buffer_rsrc_t Buffer;
 __device__ __forceinline__ Buffer make_buffer(const void* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000);

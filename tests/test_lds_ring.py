@@ -1,4 +1,7 @@
-"""LDS rings: no wave may pass a barrier with reads of the stage before in flight.
+"""LDS rings, looked at in the assembly: what a barrier hands on, and which rows a
+stage's loads may reach.
+
+No wave may pass a barrier with reads of the stage before in flight.
 
 The staged kernels hand a ring's stage on at a barrier: behind it the waves
 refill the stage that the previous step read.  A read that a wave has issued but
@@ -118,3 +121,19 @@ def test_no_load_between_the_wait_and_its_barrier(assembly, kernel):
                     back = code[:k][::-1]
                     wait = next(j for j, b in enumerate(back) if "vmcnt" in b)
                     assert not [b for b in back[:wait] if re.search(r"load_lds|\blds$", b)], name
+
+
+def test_rows_past_the_batch_are_kept_out_by_the_lane_offset(assembly):
+    """The last M-block of the 256 x 256 tile addresses rows past M.  Its buffer ends
+    at row M, and the bounds check is certain only of the lane's offset, not of the
+    uniform one: the eight loads of an A stage, 32 rows apart, must differ in the
+    lane's offset and share the uniform one."""
+    forms = [body for name, body in assembly.items() if "gemm_bf16_wide" in name]
+    assert len(forms) == 2
+    for body in forms:
+        loads = re.findall(r"buffer_load_dwordx4 (v\d+), s\[[\d:]+\], (\w+) offen(.*)", body)
+        a = [(lane, uniform) for lane, uniform, flags in loads if "nt" not in flags.split()]
+        assert a and len(a) % 8 == 0
+        for i in range(0, len(a), 8):
+            assert len({lane for lane, _ in a[i:i + 8]}) == 8
+            assert len({uniform for _, uniform in a[i:i + 8]}) == 1
