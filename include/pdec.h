@@ -300,7 +300,9 @@ int kv_import(pdec_engine* engine, int32_t seq, const void* host_src, int64_t sr
 
 /* Next tokens from logits: mode 0 = greedy argmax, ties to the lowest id
  * (the paper does not state its sampler).  logits_dev: device fp32
- * [batch][vocab]; tokens_dev_out: device int32 [batch].
+ * [batch][vocab]; tokens_dev_out: device int32 [batch].  A call touches these
+ * two buffers and nothing of the engine's, so calls put on several streams
+ * (engine_set_stream, a replayed graph) may overlap.
  * Errors: PDEC_UNSUPPORTED for any other mode, PDEC_INVALID_ARG. */
 int sample(pdec_engine* engine, int32_t batch, const float* logits_dev, int32_t* tokens_dev_out,
            int32_t mode);

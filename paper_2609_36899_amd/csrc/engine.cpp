@@ -197,17 +197,13 @@ class LaunchTimer {
 // Workspace layout.
 // ---------------------------------------------------------------------------
 struct WsLayout {
-  size_t rope, bt, meta, delta, x, h, o, u, q, lmg, part, att_ml, att_acc, argmax, total;
+  size_t rope, bt, meta, delta, x, h, o, u, q, lmg, part, att_ml, att_acc, total;
   size_t meta_bytes, part_elems, delta_cap;
   int64_t items_cap, qblocks_cap, rows_cap, part_row_slots;
   int32_t bt_stride;
 };
 
 constexpr size_t kDeltaCap = 65536;
-// Scratch slots of sample, taken in turn: unlike the forward passes, greedy
-// sampling needed no workspace, so a caller may have put a call on another stream
-// (engine_set_stream) beside the ones around it.
-constexpr int kArgmaxSlots = 8;
 // Sequence pieces one prefill pass may hold (kv_append_prefix_batch packs
 // several sequences' tokens into one pass); also the most LM-head rows a
 // prefill pass produces.
@@ -335,7 +331,6 @@ int make_layout(const pdec_model_cfg* c, int32_t max_seqs, int32_t max_seq_len,
   L->part = take(L->part_elems * 4);
   L->att_ml = take((size_t)L->part_row_slots * c->n_kv_heads * 2 * 4);
   L->att_acc = take((size_t)L->part_row_slots * c->n_kv_heads * c->head_dim * 4);
-  L->argmax = take((size_t)kArgmaxSlots * kArgmaxPairs * 8);
   L->total = off;
   return PDEC_OK;
 }
@@ -374,7 +369,6 @@ struct pdec_engine {
   std::vector<char> host_meta;
   std::vector<int32_t> mark;
   int32_t epoch = 0;
-  uint32_t sample_calls = 0;
   // PDEC_VALIDATE=1 at engine creation: every pass's rows, query blocks,
   // items, pages and pending block-table entries are bounds-checked on the
   // host before anything is enqueued.
@@ -1042,9 +1036,7 @@ int sample(pdec_engine* E, int32_t B, const float* logits_dev, int32_t* tokens_d
   if (!E || !logits_dev || !tokens_dev_out) return fail(PDEC_INVALID_ARG, "null argument");
   if (mode != 0) return fail(PDEC_UNSUPPORTED, "only greedy sampling (mode 0) is implemented");
   if (B < 1) return fail(PDEC_INVALID_ARG, "batch must be >= 1");
-  char* scratch = E->base + E->ws.argmax + (E->sample_calls++ % kArgmaxSlots) * kArgmaxPairs * 8;
-  HIP_OR_FAIL(launch_argmax(B, E->cfg.vocab, logits_dev, tokens_dev_out, scratch, kArgmaxPairs * 8,
-                            E->stream));
+  HIP_OR_FAIL(launch_argmax(B, E->cfg.vocab, logits_dev, tokens_dev_out, E->stream));
   return PDEC_OK;
 }
 

@@ -11,6 +11,8 @@ namespace pdec {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// The same where only the elements are aligned; one 16-byte global load all the same.
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
 typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));

@@ -150,12 +150,8 @@ hipError_t launch_sum_splits(int64_t n, const float* part, int splits, float* ou
 // dst[i] = src[idx[i]] for n rows of row_bytes bytes (row_bytes % 4 == 0).
 hipError_t launch_gather_rows(int n, const int32_t* idx, const void* src, int64_t row_bytes,
                               void* dst, hipStream_t stream);
-// tokens[b] = argmax_v logits[b][v] (lowest index on ties).  scratch (nullable):
-// kArgmaxPairs (row, chunk) results of 8 bytes; without it one work group takes
-// each row.
-constexpr int kArgmaxPairs = 512;
-hipError_t launch_argmax(int B, int V, const float* logits, int32_t* tokens, void* scratch,
-                         int64_t scratch_bytes, hipStream_t stream);
+// tokens[b] = argmax_v logits[b][v] (lowest index on ties).
+hipError_t launch_argmax(int B, int V, const float* logits, int32_t* tokens, hipStream_t stream);
 // bt[d.slot * stride + d.idx] = d.page for each delta.
 hipError_t launch_bt_deltas(int n, const BtDelta* deltas, int32_t* bt, int32_t stride,
                             hipStream_t stream);

@@ -53,6 +53,39 @@ def test_greedy_chunks(vocab, offset):
         np.testing.assert_array_equal(tok.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("vocab,B", [(128256, 48), (65536, 3)])
+def test_greedy_calls_may_overlap(vocab, B):
+    """24 outstanding calls over two streams that wait for nothing, eight of them
+    replays of one captured call: each gives its own rows' tokens."""
+    from workload import TINY
+    import paper_2609_36899_amd as P
+    E = _engine(dataclasses.replace(TINY, n_layers=1, d_model=64, ffn_dim=64, vocab=vocab), P.F32)
+    n = 24
+    z = torch.randn((n, B, vocab), device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    tok = torch.full((n, B), -1, dtype=torch.int32, device="cuda")
+    replayed = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+    sides = [torch.cuda.Stream(), torch.cuda.Stream()]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        E.set_stream(torch.cuda.current_stream())
+        E.sample(z[0], replayed)
+    torch.cuda.synchronize()
+    seen = []
+    for i in range(n):
+        E.set_stream(sides[i % 2])
+        E.sample(z[i], tok[i])
+        if i % 3 == 0:  # in order among themselves, beside the calls of the other stream
+            with torch.cuda.stream(sides[0]):
+                replayed.fill_(-1)
+                graph.replay()
+                seen.append(replayed.clone())
+    torch.cuda.synchronize()
+    E.set_stream(torch.cuda.current_stream())
+    want = z.argmax(dim=2)
+    assert torch.equal(tok.long(), want)
+    assert all(torch.equal(s.long(), want[0]) for s in seen)
+
+
 @pytest.mark.parametrize("kind", ["f32", "bf16", "fp8"])
 @pytest.mark.parametrize("before", [0, 5, 8, 16, 27])
 def test_v_rows_match_single_rows(kind, before):
