@@ -6,6 +6,8 @@
 #include "hip_common.h"
 #include "kernels.h"
 
+#include <type_traits>
+
 namespace pdec {
 
 namespace {
@@ -362,7 +364,7 @@ __device__ __forceinline__ void argmax_merge(float& v, int& i, float v2, int i2)
   }
 }
 
-// One work group of 1024 threads per row, or per chunk of `span` tokens of a row (a
+// One work group of up to 1024 threads per row, or per chunk of `span` tokens of a row (a
 // multiple of 4).  Ties go to the lowest index.  Four 16-byte loads in flight per
 // thread; rows need no more than their own four-byte alignment, and loads past the
 // end repeat the chunk's last four tokens.
@@ -372,21 +374,25 @@ __device__ __forceinline__ void argmax_merge(float& v, int& i, float v2, int i2)
 // calls, which may overlap in any way (sample takes no workspace), and the result does
 // not depend on the order.  It starts at token 0 (argmax_start_kernel), which any number
 // beats where that logit is NaN.
-constexpr int kArgmaxLoads = 4;
 __device__ __forceinline__ void argmax_span(const float* lr, int i0, int i1, float& best, int& bi) {
   const int n = blockDim.x, t = threadIdx.x, q_end = i1 / 4;
-  for (int q0 = i0 / 4; q0 < q_end; q0 += n * kArgmaxLoads) {
-    f32x4_any v[kArgmaxLoads];
+  int q0 = i0 / 4;
+  auto take = [&](auto loads) {
+    constexpr int L = decltype(loads)::value;
+    f32x4_any v[L];
 #pragma unroll
-    for (int u = 0; u < kArgmaxLoads; ++u)
+    for (int u = 0; u < L; ++u)
       v[u] = *(const f32x4_any*)(lr + (int64_t)min(q0 + u * n + t, q_end - 1) * 4);
 #pragma unroll
-    for (int u = 0; u < kArgmaxLoads; ++u) {
+    for (int u = 0; u < L; ++u) {
       const int at = min(q0 + u * n + t, q_end - 1) * 4;
 #pragma unroll
       for (int k = 0; k < 4; ++k) argmax_merge(best, bi, v[u][k], at + k);
     }
-  }
+    q0 += L * n;
+  };
+  while (q0 + 3 * n < q_end) take(std::integral_constant<int, 4>{});
+  while (q0 < q_end) take(std::integral_constant<int, 1>{});
   const int rest = max(i0, q_end * 4) + t;  // the row's last tokens past whole fours
   if (rest < i1) argmax_merge(best, bi, lr[rest], rest);
 }
@@ -583,7 +589,7 @@ hipError_t launch_argmax(int B, int V, const float* logits, int32_t* tokens, hip
   // rows on the rows alone fill the GPU, and shorter rows are read as fast by one
   // group (32003 tokens: 6.7 against 7.8).
   if (V < 65536 || B > 64) {
-    argmax_kernel<<<B, 1024, 0, stream>>>(V, V, logits, tokens);
+    argmax_kernel<<<B, row_threads(V), 0, stream>>>(V, V, logits, tokens);
     return hipGetLastError();
   }
   const int span = (int)((((int64_t)V + 3) / 4 + 3) / 4 * 4);
