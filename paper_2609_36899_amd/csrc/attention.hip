@@ -21,6 +21,8 @@
 #include "hip_common.h"
 #include "kernels.h"
 
+#include <type_traits>
+
 namespace pdec {
 
 namespace {
@@ -447,24 +449,36 @@ __global__ __launch_bounds__(256) void attn_split_f32(
       // A wave reads back only what it wrote; LDS operations of one wave keep
       // their order, the fence keeps the compiler from moving the reads up.
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      // Weights of keys past a row's causal limit are 0, but 0 times such a key's V
+      // is not where that is inf or NaN: in the tiles that a row's limit cuts (none
+      // with one query token) the row takes those V as 0.
+      auto weigh = [&](auto cut) {
+        constexpr bool kCut = decltype(cut)::value;
 #pragma unroll 2
-      for (int k = 0; k < T; k += 4) {
-        f32x4 v[E];
+        for (int k = 0; k < T; k += 4) {
+          f32x4 v[E];
 #pragma unroll
-        for (int e = 0; e < E; ++e) v[e] = *(const f32x4*)(vs + (lane + 64 * e) * VS + k);
+          for (int e = 0; e < E; ++e) v[e] = *(const f32x4*)(vs + (lane + 64 * e) * VS + k);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const f32x4 p = *(const f32x4*)(ps + (i0 + i) * 4 * T + wave * T + k);
+          for (int i = 0; i < 4; ++i) {
+            const f32x4 p = *(const f32x4*)(ps + (i0 + i) * 4 * T + wave * T + k);
+            const int left = qb.pos0 + (4 * (i0 + i) + wave) / G + 1 - (key0 + t0 + k);
 #pragma unroll
-          for (int e = 0; e < E; ++e) {
-            float a = acc[i0 + i][e];
-            a = fmaf(p.x, v[e].x, a);
-            a = fmaf(p.y, v[e].y, a);
-            a = fmaf(p.z, v[e].z, a);
-            acc[i0 + i][e] = fmaf(p.w, v[e].w, a);
+            for (int e = 0; e < E; ++e) {
+              float a = acc[i0 + i][e];
+              a = fmaf(p.x, !kCut || left > 0 ? v[e].x : 0.f, a);
+              a = fmaf(p.y, !kCut || left > 1 ? v[e].y : 0.f, a);
+              a = fmaf(p.z, !kCut || left > 2 ? v[e].z : 0.f, a);
+              acc[i0 + i][e] = fmaf(p.w, !kCut || left > 3 ? v[e].w : 0.f, a);
+            }
           }
         }
-      }
+      };
+      const int first_lim = qb.pos0 + (4 * i0 + wave) / G + 1;  // of the four rows' limits
+      if (first_lim < min(kv_lim, key0 + t0 + T))
+        weigh(std::true_type{});
+      else
+        weigh(std::false_type{});
     }
   }
 #pragma unroll

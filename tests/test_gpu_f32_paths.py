@@ -77,3 +77,33 @@ def test_projection_rows(M, N, K, shift):
     tol = 1.1 * bound * np.abs(up) + eps * (np.abs(x64) @ np.abs(u64).T) * np.abs(g) + \
         8 * 2.0 ** -24 * np.abs(ref) + 1e-30
     assert np.all(np.abs(u.cpu().numpy() - ref) <= tol)
+
+
+@pytest.mark.parametrize("n,bad", [(20, 19), (40, 17), (200, 199), (200, 70)])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_prefill_rows_do_not_see_later_tokens(n, bad, value):
+    """A token whose embedding is not finite has K and V that are not: earlier tokens,
+    in its query block too, must not take anything from it.  Their layer-1 K and V,
+    which depend on layer 0's attention, are compared with those of the same tokens
+    with another one in its place: the same sums."""
+    import paper_2609_36899_amd as P
+    from workload import TINY, make_weights, random_tokens
+    w = make_weights(TINY, seed=3, bf16=False)
+    toks = random_tokens(n, TINY.vocab, 5)
+    marked, plain = TINY.vocab - 1, TINY.vocab - 2
+    toks = [t if t < plain else 0 for t in toks]
+    w["embed"] = w["embed"].copy()
+    w["embed"][marked] = value
+    kv = []
+    for tok in (plain, marked):
+        E = P.Engine(TINY, P.weights_to_device(w, P.F32), P.F32,
+                     16 * 16 * P.kv_bytes_per_token(TINY, P.F32), max_seqs=1, max_seq_len=256,
+                     max_batch=1, max_chunk=256)
+        s = E.kv_alloc(0)
+        E.kv_append_prefix(s, toks[:bad] + [tok] + toks[bad + 1:], chunk_tokens=256)
+        at = torch.arange(n, device="cuda")
+        pg = torch.from_numpy(E.kv_block_table(s)).cuda().long()[at // 16]
+        kv.append((E.k_pages(1)[pg, :, at % 16].clone(), E.v_pages(1)[pg, :, :, at % 16].clone()))
+    for want, got in zip(*kv):
+        assert not torch.isfinite(got[bad]).all()
+        assert torch.equal(got[:bad], want[:bad]) and torch.isfinite(want).all()
