@@ -726,7 +726,7 @@ __global__ __launch_bounds__(256) void gemm_f32_tiled(int M, int N, int K, int k
 }
 
 // fp32, up to 16 rows: a wave owns NC columns and every row (MP >= M), its lanes
-// take K in steps of 256 (16 bytes of each weight row and activation row), and
+// take K in steps of 256 (four elements of each weight row and activation row), and
 // the NC * MP lane sums are reduced together: each of the first log2(NC * MP)
 // exchange steps halves the number of values a lane carries, so 16 values cost
 // 17 exchanges instead of 96, and lane i ends with one finished value.  One wave
@@ -754,11 +754,12 @@ __global__ __launch_bounds__(64) void gemm_f32_rows(int M, int N, int K,
   for (int i = 0; i < V; ++i) v[i] = 0.f;
 #pragma unroll 2
   for (int k = lane * 4; k < K; k += 256) {  // K % 4 == 0
-    float4 a[MP], b[NW];
+    f32x4_any a[MP], b[NW];
 #pragma unroll
-    for (int c = 0; c < NW; ++c) b[c] = *(const float4*)(wr[c] + k);
+    for (int c = 0; c < NW; ++c) b[c] = *(const f32x4_any*)(wr[c] + k);
 #pragma unroll
-    for (int m = 0; m < MP; ++m) a[m] = *(const float4*)(A + (int64_t)min(m, M - 1) * lda + k);
+    for (int m = 0; m < MP; ++m)
+      a[m] = *(const f32x4_any*)(A + (int64_t)min(m, M - 1) * lda + k);
 #pragma unroll
     for (int c = 0; c < NW; ++c)
 #pragma unroll
@@ -876,12 +877,12 @@ static bool strip_form(int M, int K, int64_t groups) {
   return M <= 16 && groups <= 32 && (int64_t)M * K <= 131072;
 }
 
-// The fp32 kernel for few rows reads 16 bytes of weight and activation rows at
-// a time; above 16 rows its per-wave weight reads would be repeated by more
-// waves than the tiled kernel's.
+// The fp32 kernel for few rows reads four elements of weight and activation rows
+// at a time, whatever their alignment (the split count is planned from the shape
+// alone); above 16 rows its per-wave weight reads would be repeated by more waves
+// than the tiled kernel's.
 constexpr int kF32RowsMax = 16;
 static bool f32_rows_shape(int M, int K) { return M <= kF32RowsMax && K % 4 == 0; }
-static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 int gemm_plan_splits(int dtype, int M, int N, int K, int* k_split, bool glu) {
   const int kq = (dtype == 1) ? 64 : 16;
@@ -1065,8 +1066,7 @@ bool launch_gemm_f32_swiglu(int M, int F, int K, const float* A, const float* w_
                             const float* w_up, float* u, hipStream_t stream, hipError_t* err,
                             hipEvent_t ev_start, hipEvent_t ev_stop) {
   *err = hipSuccess;
-  if (!f32_rows_shape(M, K) || !aligned16(A) || !aligned16(w_gate) || !aligned16(w_up))
-    return false;
+  if (!f32_rows_shape(M, K)) return false;
   WSegs w{};
   w.ptr[0] = w_gate;
   w.ptr[1] = w_up;
@@ -1094,9 +1094,7 @@ hipError_t launch_gemm(int dtype, int M, int N, int K, const void* A, int64_t ld
     return launch_gemm_bf16<false>(M, N, K, (const uint16_t*)A, lda, w, n_groups, out, nullptr,
                                    splits, k_split, stream, ev_start, ev_stop);
   } else {
-    if (splits == 1 && f32_rows_shape(M, K) && lda % 4 == 0 && aligned16(A) &&
-        aligned16(w_in.ptr[0]) && (w_in.n_seg < 2 || aligned16(w_in.ptr[1])) &&
-        (w_in.n_seg < 3 || aligned16(w_in.ptr[2])))
+    if (splits == 1 && f32_rows_shape(M, K))
       return launch_f32_rows<false>(M, N, K, (const float*)A, lda, w_in, out, stream, ev_start,
                                     ev_stop);
     const dim3 grid((N + 63) / 64, (M + 31) / 32, splits);

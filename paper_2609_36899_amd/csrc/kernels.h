@@ -95,7 +95,7 @@ hipError_t launch_gemm_swiglu(int M, int F, int K, const void* A, int64_t lda, c
                               hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 // fp32 gate/up projection with SwiGLU for up to kF32RowsMax rows in one kernel
 // (u[m][n] as launch_gemm over the two segments and launch_swiglu give it);
-// false where the shape or an alignment rules it out and nothing was enqueued.
+// false where the shape rules it out and nothing was enqueued.
 bool launch_gemm_f32_swiglu(int M, int F, int K, const float* A, const float* w_gate,
                             const float* w_up, float* u, hipStream_t stream, hipError_t* err,
                             hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);

@@ -5,7 +5,7 @@ Attention: context lengths around the 16-token pages, the 64-key tiles and the
 groups that fill a wave's rows unevenly, slots past a context's end NaN.
 Projections: row counts around each form of the few-row kernel and its limit of
 16, K around its 256-wide steps, columns that do not fill a wave, and inputs
-that are not 16-byte aligned (the tiled kernel).
+that are not 16-byte aligned (the same sums).
 
 Tolerances: a lane adds at most K/64 + 16 products (attention: dims, then keys)
 in a chain of fp32 roundings, so |error| <= (n + 16) 2^-24 sum |a||b| for a
@@ -77,6 +77,32 @@ def test_projection_rows(M, N, K, shift):
     tol = 1.1 * bound * np.abs(up) + eps * (np.abs(x64) @ np.abs(u64).T) * np.abs(g) + \
         8 * 2.0 ** -24 * np.abs(ref) + 1e-30
     assert np.all(np.abs(u.cpu().numpy() - ref) <= tol)
+
+
+@pytest.mark.parametrize("M", [1, 4, 8, 16])
+@pytest.mark.parametrize("shift", [1, 2])
+def test_projection_rows_of_any_alignment(M, shift):
+    """Activations and weights that start at an element's own alignment take the same
+    kernel as aligned ones: the same bits."""
+    import paper_2609_36899_amd as P
+    N, K = 516, 688
+    gen = torch.Generator("cuda").manual_seed(M)
+    x, w, w2 = (torch.randn(s, device="cuda", generator=gen) for s in ((M, K), (N, K), (N, K)))
+
+    def off(t):  # the same values at an odd place
+        buf = torch.empty(shift + t.numel(), device="cuda")
+        buf[shift:].copy_(t.flatten())
+        return buf[shift:].view(t.shape)
+
+    res = []
+    for f in (lambda t: t, off):
+        pw = [P.PackedWeight(f(t), N, K, P.F32) for t in (w, w2)]  # fp32: row-major as it is
+        out, u = torch.empty((M, N), device="cuda"), torch.empty((M, N), device="cuda")
+        P.weight_projection(f(x), pw[0], out)
+        P.swiglu_projection(f(x), pw[0], pw[1], u)
+        res.append((out, u))
+    for a, b in zip(*res):
+        assert torch.equal(a, b)
 
 
 @pytest.mark.parametrize("n,bad", [(20, 19), (40, 17), (200, 199), (200, 70)])
