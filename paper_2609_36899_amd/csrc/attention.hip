@@ -381,8 +381,8 @@ __global__ __launch_bounds__(256) void attn_split_f32(
       const int f = j * 256 + tid, pg = f / (4 * DH), w = f % (4 * DH);
       const int64_t base =
           (int64_t)btrow[min(t0 / kPage + pg, it.n_pages - 1)] * page_stride + head_off + w * 4;
-      kr[j] = *(const f32x4*)(kpool + base);
-      vr[j] = *(const f32x4*)(vpool + base);
+      kr[j] = *(const f32x4_any*)(kpool + base);
+      vr[j] = *(const f32x4_any*)(vpool + base);
     }
   };
   auto store = [&](int t0) {

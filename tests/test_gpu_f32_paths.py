@@ -52,6 +52,24 @@ def test_attention_tile_edges(hq, hkv, dh, lens):
         assert np.max(np.abs(got[b] - ref)) <= tol
 
 
+def test_attention_pages_of_any_alignment():
+    """Pools that start at an element's own alignment: the same bits."""
+    import paper_2609_36899_amd as P
+    from workload import paged_attention_case
+    lens = (1, 17, 130, 400)
+    case = paged_attention_case(4, 4, 2, 64, np.array(lens), 60, seed=3, bf16=False)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    bt, q = dev(np.maximum(case.block_table, 0)), dev(case.q)
+    k, v = dev(np.nan_to_num(case.k_pool)), dev(np.nan_to_num(case.v_pool).transpose(0, 1, 3, 2))
+    res = []
+    for shift in (0, 1, 2):
+        at = lambda t: torch.cat([torch.zeros(shift, device="cuda"), t.flatten()])[shift:].view(t.shape)
+        out = torch.empty((4, 4, 64), device="cuda")
+        P.paged_decode_attention(q, at(k), at(v), bt, lens, out)
+        res.append(out)
+    assert torch.equal(res[1], res[0]) and torch.equal(res[2], res[0])
+
+
 @pytest.mark.parametrize("M", [1, 2, 3, 4, 5, 8, 9, 16, 17])
 @pytest.mark.parametrize("N,K,shift", [(4, 4, 0), (516, 252, 0), (1024, 256, 0), (260, 688, 0),
                                        (64, 1030, 0), (132, 256, 1)])

@@ -53,6 +53,17 @@ def test_greedy_chunks(vocab, offset):
         np.testing.assert_array_equal(tok.cpu().numpy(), want)
 
 
+def test_greedy_more_rows_than_a_grid_axis():
+    """70000 rows: only the first grid axis takes that many work groups."""
+    import paper_2609_36899_amd as P
+    from workload import TINY
+    E = _engine(dataclasses.replace(TINY, n_layers=1, d_model=64, ffn_dim=64, vocab=64), P.F32)
+    z = torch.randn((70000, 64), device="cuda", generator=torch.Generator("cuda").manual_seed(2))
+    tok = torch.full((70000,), -1, dtype=torch.int32, device="cuda")
+    E.sample(z, tok)
+    assert torch.equal(tok.long(), z.argmax(dim=1))
+
+
 @pytest.mark.parametrize("vocab,B", [(128256, 48), (65536, 3)])
 def test_greedy_calls_may_overlap(vocab, B):
     """24 outstanding calls over two streams that wait for nothing, eight of them
