@@ -500,7 +500,8 @@ int enqueue_forward(pdec_engine* E, const Pass& p, const int32_t* tokens_dev, fl
                                    E->rope_cs, E->bt, E->ws.bt_stride, E->q, E->k_layer(l),
                                    E->v_layer(l), E->page_stride,
                                    c.qk_norm ? E->q_norm[l] : nullptr,
-                                   c.qk_norm ? E->k_norm[l] : nullptr, c.rms_eps, s));
+                                   c.qk_norm ? E->k_norm[l] : nullptr, c.rms_eps,
+                                   rows_per_item != kDecodeRows, s));
     HIP_OR_FAIL(E->timer.pair(PDEC_TIMER_ATTENTION, &ea, &eb));
     HIP_OR_FAIL(launch_attention_split(dt, c.kv_fp8, c.kv_scale_k, c.kv_scale_v, Dh, rows_per_item,
                                        n_items, c.n_q_heads, c.n_kv_heads,

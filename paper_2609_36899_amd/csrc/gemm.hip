@@ -255,9 +255,9 @@ __global__ __launch_bounds__(64 * kStripWaves) void gemm_bf16_strip(
 // while step it is computed, steps it+1 .. it+D-1 are in flight.  One barrier per
 // step: after it, every wave has finished step it-1, whose stage then takes step
 // it+D-1.  Up to 64 rows the weight stream is the bound and what is in flight
-// sets its rate: two stages of 16 KiB per CU gave gate/up 5.0 TB/s at 64 rows
-// (45.8 us), five (D = 6, 24 KiB stages) 5.7 (40.9).  From 128 rows on a fourth
-// stage measured level or slower.
+// sets its rate: the 128-row tile's two stages give gate/up 5.3 TB/s at 64 rows
+// (44.4 us), five of this tile (D = 6, 24 KiB stages) 5.7 (40.9).  From 128 rows on a
+// fourth stage measured level or slower.
 // The W tile (one packed group, 2 k-blocks x 8 strips) is one contiguous
 // 16 KiB run in HBM, copied in packed order (fragment reads from LDS are
 // linear, hence free of bank conflicts) with the non-temporal hint, so the
@@ -365,8 +365,9 @@ __global__ __launch_bounds__(8 * ROWS / MT) void gemm_bf16_tile(int M, int N, in
   };
   // The step in stage b, with the loads of step i_next: one behind each row of MFMAs
   // where they fit (all at once, eight waves stall on the 64 bytes a cycle of the
-  // texture path: FFN of the 14B shape at 200 rows 1% slower, tool-output append
-  // 0.5%), or all ahead of them (the 64-row tile, which lives on loads in flight).
+  // texture path; us, spread / at once: gate/up of the 8B shape at 160 rows 55 / 60,
+  // of the 14B shape at 200 rows 104 / 107, down of the 8B shape at 1463 rows 170 /
+  // 185), or all ahead of them (the 64-row tile, which lives on loads in flight).
   constexpr bool kSpread = 2 * MT >= LPS;
   auto compute = [&](int b, int i_next, int b_next) {
     if constexpr (!kSpread) {
@@ -815,10 +816,10 @@ constexpr int kStreamMaxRows = 32;
 
 // Row tiles of the 128-column kernel: 64, 128, 192 or 256 rows, so that up to 256
 // rows W is read once per step by the smallest tile that holds the batch.
-// Measured (us, against the tile the batch took before, 128 rows up to 128 and 256
-// above): gate/up 40.9 / 45.8 at 64 rows, 59.1 / 64.2 at 192, down 36.6 / 39.9 at
-// 160.  Up to 64 rows a long K split over the grid (down: 28 k-steps of 64 per
-// work group) is 2-3% faster on the 128-row tile.
+// Measured (us, against the 128-row tile up to 128 rows and the 256-row tile above):
+// gate/up 40.9 / 44.4 at 64 rows, 58.9 / 63.8 at 192, down 37.0 / 39.9 at 160.  Up
+// to 64 rows a long K split over the grid (down: 28 k-steps of 64 per work group) is
+// 2-3% faster on the 128-row tile.
 //
 // Above 256 rows (kRowStep steps) the tile and the K splits are chosen together.
 // The grid rarely fills whole rounds of the 256 CUs, and what a round costs is
@@ -829,7 +830,9 @@ constexpr int kStreamMaxRows = 32;
 // plus the splits' partial sums written and read at about 5 TB/s.  Against
 // 256-row tiles with the splits planned alone: qkv 97.7 / 108.3 at 1400 rows (two
 // rounds of 192 instead of one and an eighth of 256), 44.6 / 52.1 at 600 (128-row
-// tiles), down 174 / 191 at 1400 and 60.7 / 68.3 at 300.
+// tiles), down 174 / 191 at 1400 and 60.7 / 68.3 at 300.  Not everywhere: o at 2048
+// rows, one full round of 256-row tiles either way, takes 65-69 us where 65.1 was
+// measured before the loads were spread.
 //
 // The 256 x 256 tile enters the same comparison, unsplit and at 102 us a round (o of
 // the 8B shape at 4096 rows, one round: 102 us; 115 on eight waves of 64 x 128), from

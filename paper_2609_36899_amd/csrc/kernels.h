@@ -132,13 +132,14 @@ hipError_t launch_resid_norm(int dtype, int M, int d, const float* part, int spl
                              const float* gain, float eps, void* h, hipStream_t stream);
 // Sum the q|k|v partials, rotate q and k at each row's position (cos/sin
 // table [pos][head_dim/2] of float2), write q to q_out [M][Hq][Dh] and k, v
-// into the row's page slot of this layer's pool.
+// into the row's page slot of this layer's pool.  runs: rows are mostly runs of one
+// sequence's consecutive tokens (prefill), which chooses how V is written.
 hipError_t launch_qkv_rope_kv(int dtype, int kv_fp8, float k_scale, float v_scale, int M,
                               int head_dim, int n_q_heads, int n_kv_heads, const float* part,
                               int splits, const RowMeta* rows, const float2* rope_cs,
                               const int32_t* block_table, int32_t bt_stride, void* q_out,
                               void* k_pages, void* v_pages, int64_t page_stride_elems,
-                              const float* q_gain, const float* k_gain, float eps,
+                              const float* q_gain, const float* k_gain, float eps, bool runs,
                               hipStream_t stream);
 // u[m][n] = silu(g) * up with g, up the summed partials of columns n and F+n.
 // Row m of u starts at u + m * ldu (ldu 0: F).

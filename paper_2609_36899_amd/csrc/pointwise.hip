@@ -215,7 +215,7 @@ __global__ __launch_bounds__(1024) void resid_norm_kernel(
 // Work groups [0, M * n_parts) take a row's q and k quads (and, with v_rows = 1,
 // its v quads), one per thread; the partial sums are asked for before the row's
 // position and page, which only the stores and the table read need.  v_rows = 16
-// (many rows): work groups of their own take 16 consecutive rows of one KV head,
+// (prefill): work groups of their own take 16 consecutive rows of one KV head,
 // thread (dim, eight rows), so that the rows of a page, whose V elements lie side
 // by side, are written by one thread and, where they are eight slots of one page,
 // with one store; a row at a time, 4096 rows sent every 32-byte sector 16
@@ -527,12 +527,14 @@ hipError_t launch_qkv_rope_kv(int dtype, int kv_fp8, float k_scale, float v_scal
                               int splits, const RowMeta* rows, const float2* rope_cs,
                               const int32_t* block_table, int32_t bt_stride, void* q_out,
                               void* k_pages, void* v_pages, int64_t page_stride_elems,
-                              const float* q_gain, const float* k_gain, float eps,
+                              const float* q_gain, const float* k_gain, float eps, bool runs,
                               hipStream_t stream) {
   if (M == 0) return hipSuccess;
-  // One quad per thread.  From 64 rows on v takes work groups of its own, 16
-  // rows each; below that a row's v quads run beside its q and k quads.
-  const int v_rows = M >= 64 ? 16 : 1;
+  // One quad per thread.  Where the rows are runs of a sequence's tokens (prefill),
+  // from 64 of them on v takes work groups of its own, 16 rows each; otherwise a
+  // row's v quads run beside its q and k quads (a decode batch shares no page: 256
+  // rows took 14.3 us in the form for runs, 10.8 here).
+  const int v_rows = runs && M >= 64 ? 16 : 1;
   const int n_quads = (n_q_heads + n_kv_heads) * (head_dim / 8) +
                       (v_rows == 1 ? n_kv_heads * head_dim / 4 : 0);
   const int n_parts = (n_quads + kRowThreads - 1) / kRowThreads;

@@ -441,8 +441,9 @@ def paged_decode_attention(q: torch.Tensor, k_pages: torch.Tensor, v_pages: torc
     q [B][Hq][Dh] (bf16 or fp32), k_pages [P][Hkv][16][Dh], v_pages
     [P][Hkv][Dh][16], block_table int32 [B][stride] on the device, lens on
     the host, out fp32 [B][Hq][Dh].  With ``check_pages`` the page ids the
-    kernel will read are checked against the pool size first (one copy of the
-    block table to the host).
+    kernel will read are checked against the pool size first: on the GPU, with a
+    few words copied to the host, or on the host for tables of up to seven rows
+    and 8192 entries, which are copied themselves.  Either waits for the stream.
     """
     B, Hq, Dh = q.shape
     P, Hkv, page, Dh2 = k_pages.shape

@@ -121,3 +121,34 @@ def test_v_rows_match_single_rows(kind, before):
         assert torch.all((a - b).abs() <= step * torch.maximum(a.abs(), b.abs()) + floor)
         assert (a != b).float().mean() < (1.0 if kind == "f32" else 0.01)
         assert a.abs().max() > 0
+
+
+@pytest.mark.parametrize("kind", ["f32", "bf16", "fp8"])
+def test_v_of_a_large_decode_batch(kind):
+    """72 trajectories decoded in one step and in three leave the same layer-0 pages."""
+    import paper_2609_36899_amd as P
+    from workload import SMALL_BF16, TINY, make_weights, random_tokens
+    shape, dtype = (TINY, P.F32) if kind == "f32" else (SMALL_BF16, P.BF16)
+    fp8 = (0.02, 0.03) if kind == "fp8" else None
+    w = P.weights_to_device(make_weights(shape, seed=3, bf16=kind != "f32"), dtype)
+    n, pages = 72, []
+    last = torch.tensor(random_tokens(n, shape.vocab, 9), dtype=torch.int32, device="cuda")
+    for batch in (72, 24):
+        E = P.Engine(shape, w, dtype, 3 * n * 16 * P.kv_bytes_per_token(shape, dtype, fp8), max_seqs=n,
+                     max_seq_len=64, max_batch=n, max_chunk=64, kv_fp8=fp8)
+        ids = [E.kv_alloc(0) for _ in range(n)]
+        for i, s in enumerate(ids):
+            E.kv_append_prefix(s, random_tokens(1 + i % 33, shape.vocab, i), chunk_tokens=64)
+        logits = torch.empty((n, shape.vocab), device="cuda")
+        for b in range(0, n, batch):
+            E.decode_step(ids[b:b + batch], last[b:b + batch], logits[b:b + batch])
+        at = torch.tensor([1 + i % 33 for i in range(n)], device="cuda")
+        pg = torch.tensor([int(E.kv_block_table(s)[(1 + i % 33) // 16]) for i, s in enumerate(ids)],
+                          device="cuda")
+        view = lambda t: (t.view(torch.float8_e4m3fn) if kind == "fp8" else t).float()
+        pages.append((view(E.k_pages(0))[pg, :, at % 16], view(E.v_pages(0))[pg, :, :, at % 16]))
+    step = {"f32": 2.0 ** -20, "bf16": 2.0 ** -7, "fp8": 2.0 ** -3}[kind]
+    for a, b in zip(*pages):
+        floor = 2.0 ** -9 if kind == "fp8" else 1e-6
+        assert torch.all((a - b).abs() <= step * torch.maximum(a.abs(), b.abs()) + floor)
+        assert a.abs().max() > 0
