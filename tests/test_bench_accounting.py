@@ -5,7 +5,7 @@ matrix or a doubled term would shift every reported fraction.  They are
 checked against the sizes of the 8B-shaped decoder written out matrix by
 matrix (15.01 GB of weights streamed per step besides the gathered embedding
 rows), and against brute-force enumeration of the causal (query, key) pairs
-on small inputs.
+on small inputs.  The committed counter traffic has to belong to the sources here.
 """
 
 import bench
@@ -57,3 +57,11 @@ def test_append_flops_by_enumeration():
             attn_macs = shape.n_layers * shape.n_q_heads * pairs * 2 * shape.head_dim
             assert bench.append_flops(shape, ctx0, n) == 2 * (n * macs_per_token + attn_macs)
         assert bench.append_flops(shape, 0, 12) == bench.prefill_flops(shape, 12)
+
+
+def test_attention_traffic_was_counted_on_these_sources():
+    """The bench line reports counter traffic only where the record's hash is that of the
+    attention sources; a change to them needs the counters taken again."""
+    for workload in ("decode-8b-b256-lognormal", "decode-8b-b256-lognormal-fp8kv",
+                     "decode-8b-b8-long"):
+        assert bench.load_traffic(workload), workload
