@@ -42,7 +42,7 @@
 // takes a second histogram, over the keys of the bin (cut_bin), whose pass also
 // gives each block's whole mass, so that the last pass evaluates the tokens at the
 // threshold and below instead of the members.  us, radix select / this: 256 rows
-// N(0, 0.02) 296 / 213, all equal 411 / 184; 16 rows 130 / 81 and 143 / 105.
+// N(0, 0.0004) 296 / 213, all equal 411 / 184; 16 rows 130 / 81 and 143 / 105.
 #include "hip_common.h"
 #include "kernels.h"
 
