@@ -479,7 +479,7 @@ __global__ __launch_bounds__(8 * ROWS / MT) void gemm_bf16_tile(int M, int N, in
 // Work group ids L and L + 8 share an XCD, whose 32 CUs run bands of up to
 // kBandRows M-blocks by four columns of tiles: the 12 tile edges of such a square
 // come through its L2 instead of the 18 of 16 M-blocks by two columns (what down
-// at 4096 rows reads past L2: 389 MB against 516).  K >= 128, a multiple of 64.
+// at 4096 rows reads past L2: 0.75 GB against 1.0).  K >= 128, a multiple of 64.
 constexpr int kBandRows = 8;
 template <bool GLU>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_bf16_wide(
