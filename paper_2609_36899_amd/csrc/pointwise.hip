@@ -369,11 +369,12 @@ __device__ __forceinline__ void argmax_merge(float& v, int& i, float v2, int i2)
 // thread; rows need no more than their own four-byte alignment, and loads past the
 // end repeat the chunk's last four tokens.
 //
-// Chunks merge their bests in tokens[row] itself: the row's best token so far, whose
-// logit is read again, is replaced by compare-and-swap.  So nothing is shared between
-// calls, which may overlap in any way (sample takes no workspace), and the result does
-// not depend on the order.  It starts at token 0 (argmax_start_kernel), which any number
-// beats where that logit is NaN.
+// Chunks merge their bests in tokens[row] itself: the token there, whose logit is read
+// again, is replaced by a better one with compare-and-swap.  So nothing is shared
+// between calls, which may overlap in any way (sample takes no workspace), and the
+// result depends neither on the order nor on what the buffer held: a token of the row
+// may be its best one as well as any chunk's, and what is none of its tokens is
+// replaced.  A row without a number gives token 0, which chunk 0 sees to.
 __device__ __forceinline__ void argmax_span(const float* lr, int i0, int i1, float& best, int& bi) {
   const int n = blockDim.x, t = threadIdx.x, q_end = i1 / 4;
   int q0 = i0 / 4;
@@ -424,19 +425,18 @@ __global__ __launch_bounds__(1024) void argmax_kernel(int V, int span,
     tokens[b] = (bi == 0x7FFFFFFF) ? 0 : bi;
     return;
   }
-  if (bi == 0x7FFFFFFF) return;  // no number in the chunk
+  const bool none = bi == 0x7FFFFFFF;
+  if (none && i0 > 0) return;
   int cur = __hip_atomic_load(tokens + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  for (;;) {  // the token only ever gets better: at most one turn per chunk
-    const float cv = lr[cur];
-    if (cv > best || (cv == best && cur <= bi)) return;
-    const int seen = atomicCAS(tokens + b, cur, bi);
+  for (;;) {  // a failed exchange is another chunk's, which has only one: few turns
+    if ((uint32_t)cur < (uint32_t)V) {
+      const float cv = lr[cur];
+      if (none ? cur == 0 || cv == cv : cv > best || (cv == best && cur <= bi)) return;
+    }
+    const int seen = atomicCAS(tokens + b, cur, none ? 0 : bi);
     if (seen == cur) return;
     cur = seen;
   }
-}
-
-__global__ __launch_bounds__(64) void argmax_start_kernel(int B, int32_t* tokens) {
-  if ((int)threadIdx.x < B) tokens[threadIdx.x] = 0;
 }
 
 __global__ void bt_deltas_kernel(int n, const BtDelta* __restrict__ d, int32_t* __restrict__ bt,
@@ -585,17 +585,15 @@ hipError_t launch_gather_rows(int n, const int32_t* idx, const void* src, int64_
 
 hipError_t launch_argmax(int B, int V, const float* logits, int32_t* tokens, hipStream_t stream) {
   if (B == 0) return hipSuccess;
-  // One work group reads a 128256-token row at one CU's rate; four take 10.4 us
-  // instead of 15.4 at 16 rows and 14.5 instead of 17.1 at 64, the launch of the start
-  // tokens included (more chunks wait for each other's exchanges: 17 at 32).  From 128
-  // rows on the rows alone fill the GPU, and shorter rows are read as fast by one
-  // group (32003 tokens: 6.7 against 7.8).
+  // One work group reads a 128256-token row at one CU's rate; four take 9.3 us
+  // instead of 15.4 at 16 rows and 13.4 instead of 17.1 at 64 (with more chunks they wait
+  // for each other's exchanges).  From 128 rows on the rows alone fill the GPU, and
+  // shorter rows are read as fast by one group (32003 tokens: 6.7 us).
   if (V < 65536 || B > 64) {
     argmax_kernel<<<B, row_threads(V), 0, stream>>>(V, V, logits, tokens);
     return hipGetLastError();
   }
   const int span = (int)((((int64_t)V + 3) / 4 + 3) / 4 * 4);
-  argmax_start_kernel<<<1, 64, 0, stream>>>(B, tokens);
   argmax_kernel<<<dim3(B, (V - 1) / span + 1), 1024, 0, stream>>>(V, span, logits, tokens);
   return hipGetLastError();
 }

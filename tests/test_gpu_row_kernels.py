@@ -53,6 +53,31 @@ def test_greedy_chunks(vocab, offset):
         np.testing.assert_array_equal(tok.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("held", [-1, 0, 77777, 128255, 128256, 2 ** 31 - 1, -2 ** 31])
+def test_greedy_whatever_the_buffer_held(held):
+    """Chunks merge in the output: what it held before, a token of the row or not, must
+    not matter, with numbers, ties, -inf, NaN in parts and NaN throughout."""
+    import paper_2609_36899_amd as P
+    from workload import TINY
+    V = 128256
+    E = _engine(dataclasses.replace(TINY, n_layers=1, d_model=64, ffn_dim=64, vocab=V), P.F32)
+    z = torch.randn((8, V), device="cuda", generator=torch.Generator("cuda").manual_seed(4))
+    z[1].round_()
+    z[2] = -float("inf")
+    z[3] = float("nan")
+    z[4] = float("nan")
+    z[4, V - 1] = -float("inf")
+    z[5, :77777] = float("nan")
+    z[6] = 2.0
+    z[7, V // 2:] = float("nan")
+    want = [int(np.argmax(np.where(np.isnan(r), -np.inf, r))) for r in z.cpu().numpy()]
+    want[4] = V - 1  # -inf is a number, NaN is none
+    for _ in range(3):
+        tok = torch.full((8,), held, dtype=torch.int32, device="cuda")
+        E.sample(z, tok)
+        np.testing.assert_array_equal(tok.cpu().numpy(), want)
+
+
 def test_greedy_more_rows_than_a_grid_axis():
     """70000 rows: only the first grid axis takes that many work groups."""
     import paper_2609_36899_amd as P
