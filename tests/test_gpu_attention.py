@@ -244,3 +244,9 @@ def test_check_pages_names_the_first_bad_row(B, stride, n):
         t[B - 1, 0] = 7  # a later bad row
         with pytest.raises(P.PdecError, match=f"row {row} "):
             _check_pages(torch.from_numpy(t).cuda(), lens, 7)
+
+
+@pytest.mark.parametrize("B,stride", [(1, 59500), (1, 59501), (5, 5100), (5, 5101), (7, 1214), (7, 1215)])
+def test_check_pages_of_few_long_rows(B, stride):
+    """Either side of the size from which the GPU looks, its rows split over work groups."""
+    test_check_pages_names_the_first_bad_row(B, stride, 16 * stride)
