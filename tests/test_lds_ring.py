@@ -90,7 +90,7 @@ def reads_at_barriers(body):
     return list(found.values())
 
 
-def test_checker_counts_along_paths():
+def test_wait_counts_follow_every_path():
     loop = ("ds_read_b128 v[0:3], v9\n.LBB0_1:\ns_waitcnt lgkmcnt(%d)\ns_barrier\n"
             "ds_read_b128 v[0:3], v9\nds_read_b128 v[4:7], v9\ns_cbranch_scc1 .LBB0_1\ns_endpgm\n")
     assert reads_at_barriers(loop % 0) == [0]
